@@ -30,7 +30,11 @@ CFLAGS = [
     "-Wno-unused-result", "-I", INCLUDE, "-I", CSRC,
 ]
 
-SOURCES = ["host.hip", "kernels_conv.hip", "kernels_ntt.hip", "kernels_lin.hip", "kernels_mfma.hip"]
+# (source, object, defines): the transform kernels are one unit per ring degree
+# 2^L, which compile in parallel (the largest first: they take longest).
+UNITS = [("kernels_ntt.hip", f"kernels_ntt_{L}", [f"-DFHE_NTT_L={L}"]) for L in range(14, 3, -1)]
+UNITS += [(s, os.path.splitext(s)[0], []) for s in
+          ("kernels_conv.hip", "kernels_ntt.hip", "host.hip", "kernels_lin.hip", "kernels_mfma.hip")]
 
 # Per-source device flags: the base conversions and the weighted sums on the
 # matrix cores keep their int32 sums in ordinary VGPRs (no accumulator-register
@@ -41,19 +45,20 @@ EXTRA = {
 }
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *CFLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit: tuple) -> str:
+    src, name, defines = unit
+    obj = os.path.join(OBJDIR, name + ".o")
+    cmd = [HIPCC, *CFLAGS, *EXTRA.get(src, []), *defines, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr[-6000:]}")
+        raise RuntimeError(f"hipcc failed for {name}:\n{r.stderr[-6000:]}")
     return obj
 
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

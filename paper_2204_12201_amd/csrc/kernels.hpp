@@ -53,6 +53,18 @@ enum NttMode {
 };
 
 // ---- transforms (kernels_ntt.hip) ----
+// Launches of one ring degree (the launch_* functions below pick them by c.L).
+struct NttOps {
+    hipError_t (*rows)(const DevCtx &, uint64_t *, size_t, int, int, int, hipStream_t);
+    hipError_t (*fwd_ext)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, int, size_t, hipStream_t);
+    hipError_t (*tensor)(const DevCtx &, const uint64_t *, uint64_t *, bool, size_t, hipStream_t);
+    hipError_t (*mul_tensor)(const DevCtx &, const uint64_t *, const uint64_t *, const uint64_t *, uint64_t *, size_t,
+                             hipStream_t);
+    hipError_t (*mul_tensor_pre2)(const DevCtx &, const uint64_t *, int, size_t, const uint64_t *, uint64_t *, size_t,
+                                  hipStream_t);
+    hipError_t (*square_tensor)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, size_t, hipStream_t);
+    hipError_t (*relin_fused)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, size_t, hipStream_t);
+};
 hipError_t launch_ntt_rows(const DevCtx &c, uint64_t *data, size_t nrows, int kmod, int limb_off,
                            int mode, hipStream_t s);
 // Forward transforms of the extended inputs: rows (item, poly, limb) with the

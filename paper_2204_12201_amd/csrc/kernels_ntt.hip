@@ -669,6 +669,7 @@ __global__ __launch_bounds__(Geo<L>::T) void k_relin_fused(DevCtx c, const uint6
     relin_body<L, LAZY, RAW>(c, C2, rlk, out, blockIdx.y, (int)blockIdx.x, threadIdx.x, lds, true);
 }
 
+#ifndef FHE_NTT_L
 // ---- key switching of several parts (ring sizes) in one persistent launch --
 // Every workgroup (1024 threads, one row of 16384 words of LDS plus padding)
 // takes tasks from a queue until it is empty.  A task is one (item, limb)
@@ -728,6 +729,9 @@ __global__ __launch_bounds__(1024) void k_relin_persist(const RelinQueue Q, unsi
     }
 }
 
+#endif
+
+#ifdef FHE_NTT_L
 template <int L>
 struct NttL {
     template <bool FWD, bool LZ>
@@ -870,64 +874,93 @@ struct NttL {
     }
 };
 
-#define FHE_DISPATCH_L(Lval, CALL)            \
-    switch (Lval) {                           \
-        case 4: return NttL<4>::CALL;         \
-        case 5: return NttL<5>::CALL;         \
-        case 6: return NttL<6>::CALL;         \
-        case 7: return NttL<7>::CALL;         \
-        case 8: return NttL<8>::CALL;         \
-        case 9: return NttL<9>::CALL;         \
-        case 10: return NttL<10>::CALL;       \
-        case 11: return NttL<11>::CALL;       \
-        case 12: return NttL<12>::CALL;       \
-        case 13: return NttL<13>::CALL;       \
-        case 14: return NttL<14>::CALL;       \
-        default: return hipErrorInvalidValue; \
+const NttOps kOps = {NttL<FHE_NTT_L>::rows,          NttL<FHE_NTT_L>::fwd_ext,         NttL<FHE_NTT_L>::tensor,
+                     NttL<FHE_NTT_L>::mul_tensor,    NttL<FHE_NTT_L>::mul_tensor_pre2, NttL<FHE_NTT_L>::square_tensor,
+                     NttL<FHE_NTT_L>::relin_fused};
+#endif
+
+}  // namespace
+
+// One object per ring degree 2^FHE_NTT_L (the units compile in parallel), and
+// one without FHE_NTT_L for the launches that span ring degrees.
+#ifdef FHE_NTT_L
+#define FHE_CAT2(a, b) a##b
+#define FHE_CAT(a, b) FHE_CAT2(a, b)
+const NttOps *FHE_CAT(ntt_ops_, FHE_NTT_L)() { return &kOps; }
+#else
+#define FHE_OPS(L) const NttOps *ntt_ops_##L();
+FHE_OPS(4) FHE_OPS(5) FHE_OPS(6) FHE_OPS(7) FHE_OPS(8) FHE_OPS(9) FHE_OPS(10) FHE_OPS(11) FHE_OPS(12) FHE_OPS(13)
+FHE_OPS(14)
+#undef FHE_OPS
+
+namespace {
+
+const NttOps *ops(int L) {
+    switch (L) {
+        case 4: return ntt_ops_4();
+        case 5: return ntt_ops_5();
+        case 6: return ntt_ops_6();
+        case 7: return ntt_ops_7();
+        case 8: return ntt_ops_8();
+        case 9: return ntt_ops_9();
+        case 10: return ntt_ops_10();
+        case 11: return ntt_ops_11();
+        case 12: return ntt_ops_12();
+        case 13: return ntt_ops_13();
+        case 14: return ntt_ops_14();
+        default: return nullptr;
     }
+}
 
 }  // namespace
 
 hipError_t launch_ntt_rows(const DevCtx &c, uint64_t *data, size_t nrows, int kmod, int limb_off,
                            int mode, hipStream_t s) {
-    if (nrows == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, rows(c, data, nrows, kmod, limb_off, mode, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return nrows ? o->rows(c, data, nrows, kmod, limb_off, mode, s) : hipSuccess;
 }
 
 hipError_t launch_fwd_ext(const DevCtx &c, const uint64_t *a, const uint64_t *b, uint64_t *E,
                           int npoly, size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, fwd_ext(c, a, b, E, npoly, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->fwd_ext(c, a, b, E, npoly, items, s) : hipSuccess;
 }
 
 hipError_t launch_tensor_intt(const DevCtx &c, const uint64_t *E, uint64_t *Dt, bool square,
                               size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, tensor(c, E, Dt, square, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->tensor(c, E, Dt, square, items, s) : hipSuccess;
 }
 
 hipError_t launch_mul_tensor(const DevCtx &c, const uint64_t *a, const uint64_t *b, const uint64_t *E,
                              uint64_t *Dt, size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, mul_tensor(c, a, b, E, Dt, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->mul_tensor(c, a, b, E, Dt, items, s) : hipSuccess;
 }
 
 hipError_t launch_mul_tensor_pre2(const DevCtx &c, const uint64_t *Ahat, int na, size_t item0, const uint64_t *Bhat,
                                   uint64_t *Dt, size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, mul_tensor_pre2(c, Ahat, na, item0, Bhat, Dt, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->mul_tensor_pre2(c, Ahat, na, item0, Bhat, Dt, items, s) : hipSuccess;
 }
 
 hipError_t launch_square_tensor(const DevCtx &c, const uint64_t *a, const uint64_t *E, uint64_t *Dt,
                                 size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, square_tensor(c, a, E, Dt, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->square_tensor(c, a, E, Dt, items, s) : hipSuccess;
 }
 
 hipError_t launch_relin_fused(const DevCtx &c, const uint64_t *C2, const uint64_t *rlk, uint64_t *out,
                               size_t items, hipStream_t s) {
-    if (items == 0) return hipSuccess;
-    FHE_DISPATCH_L(c.L, relin_fused(c, C2, rlk, out, items, s));
+    const NttOps *o = ops(c.L);
+    if (!o) return hipErrorInvalidValue;
+    return items ? o->relin_fused(c, C2, rlk, out, items, s) : hipSuccess;
 }
 
 hipError_t launch_relin_persist(const RelinQueue &Q, int lazy, int raw, unsigned int *queue, size_t tasks,
@@ -951,3 +984,4 @@ hipError_t launch_relin_persist(const RelinQueue &Q, int lazy, int raw, unsigned
     hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), 0, s, Q, queue);
     return hipGetLastError();
 }
+#endif
