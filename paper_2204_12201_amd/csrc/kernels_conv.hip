@@ -1152,7 +1152,16 @@ __global__ __launch_bounds__(256) void k_lift_mx(DevCtx c, const uint64_t *__res
     }
 }
 
-inline int mx_span(int n) { return n < kMxSpan ? n : kMxSpan; }
+// Coefficients per workgroup of the matrix-core conversions of `polys` rows
+// sets: kMxSpan (16 tiles a wave, which amortises staging the tables) when that
+// already gives four workgroups per CU, less (down to one tile a wave) when a
+// small batch would leave the chip idle: the scale of one product at n = 4096
+// ran 12 workgroups of 16 tiles each, 19.7 us, against 192 of one tile.
+inline int mx_span(int n, size_t polys) {
+    int span = n < kMxSpan ? n : kMxSpan;
+    while (span > 64 && (size_t)(n / span) * polys < 1024) span /= 2;
+    return span;
+}
 
 inline unsigned grid_for(size_t words, unsigned block = 256) {
     size_t g = (words + block - 1) / block;
@@ -1220,7 +1229,7 @@ hipError_t launch_lift(const DevCtx &c, const uint64_t *a, const uint64_t *b, ui
                        size_t items, hipStream_t s) {
     if (items == 0) return hipSuccess;
     if (c.mx) {
-        const int span = mx_span(c.n);
+        const int span = mx_span(c.n, npoly * items);
         hipLaunchKernelGGL(k_lift_mx, dim3(c.n / span, npoly, (unsigned)items), dim3(256), 0, s, c, a, b, E, npoly,
                            span);
         return hipGetLastError();
@@ -1232,7 +1241,7 @@ hipError_t launch_scale(const DevCtx &c, const uint64_t *Dt, uint64_t *out, uint
                         size_t items, hipStream_t s, int comp0, int ncomp) {
     if (items == 0) return hipSuccess;
     if (c.mx) {
-        const int span = mx_span(c.n);
+        const int span = mx_span(c.n, ncomp * items);
         hipLaunchKernelGGL(k_scale_mx, dim3(c.n / span, ncomp, (unsigned)items), dim3(256), 0, s, c, Dt, out, C2,
                            comp0, span);
         return hipGetLastError();
@@ -1251,7 +1260,7 @@ hipError_t launch_scale_chain(const DevCtx &c, const uint64_t *Dt, const uint64_
                               hipStream_t s) {
     if (chains == 0) return hipSuccess;
     if (c.mx) {
-        const int span = mx_span(c.n);
+        const int span = mx_span(c.n, 2 * chains);
         hipLaunchKernelGGL(k_scale_chain_mx, dim3(c.n / span, 2, (unsigned)chains), dim3(256), 0, s, c, Dt, x, E,
                            gam, R, y, tcount, span);
         return hipGetLastError();
