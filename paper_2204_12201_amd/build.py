@@ -33,6 +33,7 @@ CFLAGS = [
 # (source, object, defines): the transform kernels are one unit per ring degree
 # 2^L, which compile in parallel (the largest first: they take longest).
 UNITS = [("kernels_ntt.hip", f"kernels_ntt_{L}", [f"-DFHE_NTT_L={L}"]) for L in range(14, 3, -1)]
+UNITS += [("kernels_split.hip", f"kernels_split_{L}", [f"-DFHE_NTT_L={L}"]) for L in (12, 13, 14)]
 UNITS += [(s, os.path.splitext(s)[0], []) for s in
           ("kernels_conv.hip", "kernels_ntt.hip", "host.hip", "kernels_lin.hip", "kernels_mfma.hip")]
 

@@ -212,7 +212,7 @@ struct fhe_ctx {
     std::vector<uint64_t> enc_tw, enc_itw;
     uint64_t t_ninv = 0;
     // device allocations
-    void *d_pc = nullptr, *d_tw = nullptr, *d_itw = nullptr, *d_cc = nullptr;
+    void *d_pc = nullptr, *d_tw = nullptr, *d_itw = nullptr, *d_cc = nullptr, *d_twf = nullptr;
     void *d_mrc_q = nullptr, *d_mrc_p = nullptr, *d_counters = nullptr;
     DevCtx dev{};
     size_t batch_limit = 0, default_limit = 0;
@@ -220,6 +220,12 @@ struct fhe_ctx {
     // (item, limb) workgroups per launch on; fewer take the unfused kernels
     // (index 0: products of two ciphertexts, 1: squarings)
     size_t fused_min_rows[2] = {128, 0};
+    // launches of the split transforms (kernels_split.hip), null for other ring
+    // degrees; key switching takes them below relin_split_rows (item, limb) rows
+    // where relin_split_ok says that its sums stay in range
+    const SplitOps *split = nullptr;
+    bool relin_split_ok = false;
+    size_t relin_split_rows = 0;
     bool validate = false;
     bool timing = false;
     std::vector<EvPair> pending[KK_COUNT];
@@ -273,7 +279,7 @@ constexpr size_t kMaxPersistParts = kRelinQueueParts;
 const char *kKernelNames[KK_COUNT] = {"lift_q2p",   "square_tensor", "scale_round", "relin_fused",
                                       "ntt_rows",   "elementwise",   "bridge",      "misc",
                                       "mul_tensor", "fwd_ext",       "tensor_intt", "pass0_valu",
-                                      "pass0_mfma"};
+                                      "pass0_mfma", "split_tensor", "split_relin"};
 
 hipEvent_t take_event(fhe_ctx *c) {
     if (!c->free_events.empty()) {
@@ -366,6 +372,34 @@ fhe_status check_canonical(fhe_ctx *c, const uint64_t *a, size_t nrows, int kmod
 // threshold is 128 workgroups for products, and fhe_autotune_mul_relin moves
 // it (and the chunk size) per context from timings.
 
+// Transform phase of `items` products (squares when a == b): P rows of E from
+// the lift, tensor into Dt.  X: where the half-transformed rows may go (as
+// large as E; E itself when its P rows are not read again).
+fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64_t *E, uint64_t *X, uint64_t *Dt,
+                        size_t items, hipStream_t s) {
+    const bool square = (a == b);
+    const DevCtx &d = c->dev;
+    if (items * c->K >= c->fused_min_rows[square ? 1 : 0]) {
+        if (square)
+            return run(c, KK_SQUARE_TENSOR, s, [&] { return launch_square_tensor(d, a, E, Dt, items, s); });
+        return run(c, KK_MUL_TENSOR, s, [&] { return launch_mul_tensor(d, a, b, E, Dt, items, s); });
+    }
+    if (c->split) return run(c, KK_SPLIT_TENSOR, s, [&] { return c->split->tensor(d, a, b, E, X, Dt, square, items, s); });
+    FHE_TRY(run(c, KK_FWD_EXT, s, [&] { return launch_fwd_ext(d, a, b, E, square ? 2 : 4, items, s); }));
+    return run(c, KK_TENSOR_INTT, s, [&] { return launch_tensor_intt(d, E, Dt, square, items, s); });
+}
+
+// Key switching of C2 [items][k][n] added to out.  scratch: `words` words that
+// the split kernels may use (they need items (k^2 + 2k) n).
+fhe_status relin_phase(fhe_ctx *c, const uint64_t *C2, const uint64_t *rlk, uint64_t *out, size_t items,
+                       uint64_t *scratch, size_t words, hipStream_t s) {
+    const DevCtx &d = c->dev;
+    const size_t k = c->k;
+    if (c->relin_split_ok && items * k < c->relin_split_rows && items * (k * k + 2 * k) * c->n <= words)
+        return run(c, KK_SPLIT_RELIN, s, [&] { return c->split->relin(d, C2, rlk, scratch, out, items, s); });
+    return run(c, KK_RELIN_FUSED, s, [&] { return launch_relin_fused(d, C2, rlk, out, items, s); });
+}
+
 // The product pipeline on `count` items with workspace for min(count, limit).
 
 fhe_status mul_relin_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, const uint64_t *b,
@@ -384,18 +418,10 @@ fhe_status mul_relin_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, co
         uint64_t *C2 = Dt + items * 3 * K * n;
         const DevCtx &d = c->dev;
         FHE_TRY(run(c, KK_LIFT, s, [&] { return launch_lift(d, ai, bi, E, npoly, items, s); }));
-        if (items * K >= c->fused_min_rows[square ? 1 : 0]) {
-            if (square)
-                FHE_TRY(run(c, KK_SQUARE_TENSOR, s, [&] { return launch_square_tensor(d, ai, E, Dt, items, s); }));
-            else
-                FHE_TRY(run(c, KK_MUL_TENSOR, s, [&] { return launch_mul_tensor(d, ai, bi, E, Dt, items, s); }));
-        } else {  // few items: one workgroup per transform keeps more of the chip busy
-            FHE_TRY(run(c, KK_FWD_EXT, s, [&] { return launch_fwd_ext(d, ai, bi, E, npoly, items, s); }));
-            FHE_TRY(run(c, KK_TENSOR_INTT, s, [&] { return launch_tensor_intt(d, E, Dt, square, items, s); }));
-        }
+        FHE_TRY(tensor_phase(c, ai, bi, E, E, Dt, items, s));
         FHE_TRY(run(c, KK_SCALE, s, [&] { return launch_scale(d, Dt, oi, C2, items, s); }));
-        if (relin)
-            FHE_TRY(run(c, KK_RELIN_FUSED, s, [&] { return launch_relin_fused(d, C2, rlk, oi, items, s); }));
+        // E and Dt are free once the scale has read them
+        if (relin) FHE_TRY(relin_phase(c, C2, rlk, oi, items, E, items * (npoly + 3) * K * n, s));
     }
     return FHE_OK;
 }
@@ -422,7 +448,7 @@ fhe_status mul_relin_pre2_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *
         FHE_TRY(run(c, KK_MUL_TENSOR, s,
                     [&] { return launch_mul_tensor_pre2(d, Ahat, (int)na, off, Bhat, Dt, items, s); }));
         FHE_TRY(run(c, KK_SCALE, s, [&] { return launch_scale(d, Dt, oi, C2, items, s); }));
-        FHE_TRY(run(c, KK_RELIN_FUSED, s, [&] { return launch_relin_fused(d, C2, rlk, oi, items, s); }));
+        FHE_TRY(relin_phase(c, C2, rlk, oi, items, Dt, items * 3 * K * n, s));
     }
     return FHE_OK;
 }
@@ -463,7 +489,7 @@ void release(fhe_ctx *c) {
     if (c->join_ev) hipEventDestroy(c->join_ev);
     if (c->aux) hipStreamDestroy(c->aux);
     void *ptrs[] = {c->d_pc,       c->d_tw,  c->d_itw, c->d_cc,      c->d_mrc_q, c->d_mrc_p,
-                    c->d_counters, c->d_p0w, c->d_mx,  c->d_persist};
+                    c->d_counters, c->d_p0w, c->d_mx,  c->d_persist, c->d_twf};
     for (void *p : ptrs)
         if (p) hipFree(p);
     for (int i = 0; i < KK_COUNT; i++)
@@ -638,6 +664,22 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     if (!aux_primes(1ull << 61, ps)) return FHE_EPARAM;
     if (aux_primes(1ull << 58, ps_small) && ps_small.size() <= ps.size()) ps.swap(ps_small);
 
+    // Floating-point split transforms (kernels_split.hip: n >= 4096) where every
+    // prime of Q is below 2^50 and auxiliary primes below 2^50 need not be more
+    // in number; the smallest such cap leaves the lazy bounds most room.
+    bool f64 = n >= 4096;
+    for (uint64_t qi : qs) f64 = f64 && qi < (1ull << 50);
+    if (f64) {
+        f64 = false;
+        for (int lg = 30; lg <= 50 && !f64; lg++) {
+            std::vector<uint64_t> pf;
+            if (aux_primes(1ull << lg, pf) && pf.size() <= ps.size()) {
+                ps.swap(pf);
+                f64 = true;
+            }
+        }
+    }
+
     fhe_ctx *c = new fhe_ctx();
     c->n = n;
     c->k = k;
@@ -674,6 +716,13 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     // ---- device tables ----
     std::vector<PrimeConst> pc(c->K);
     std::vector<Tw> tw((size_t)c->K * n), itw((size_t)c->K * n);
+    std::vector<TwF> twf(f64 ? 2 * (size_t)c->K * n : 0);  // forward, then inverse
+    // w centred modulo q with its quotient by q (one correction step of v qinv)
+    auto centred = [](uint64_t w, uint64_t q, double qinv) {
+        const double v = w > q / 2 ? -(double)(int64_t)(q - w) : (double)(int64_t)w;
+        const double e = v * qinv;
+        return TwF{v, std::fma(std::fma(-e, (double)q, v), qinv, e)};
+    };
     for (uint32_t l = 0; l < c->K; l++) {
         const uint64_t q = c->primes[l];
         PrimeConst &P = pc[l];
@@ -690,18 +739,33 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
         P.mx_neg_bias = (q - (uint64_t)(((u128)FHE_MX_BIAS * 0x0101010101010101ull) % q)) % q;
         P.off59 = ((1ull << 59) + q - 1) / q * q;
         P.off62 = ((1ull << 62) + q - 1) / q * q;
+        const double qinv = 1.0 / (double)q;
+        if (f64) {
+            const TwF wn = centred(P.ninv, q, qinv), wm = centred(hinv((uint64_t)(((u128)1 << 64) % q), q), q, qinv);
+            P.pf = (double)q;
+            P.pinvf = 1.0 / (double)q;
+            P.ninvf = wn.w;
+            P.ninvf_i = wn.wi;
+            P.m64f = wm.w;
+            P.m64f_i = wm.wi;
+        }
         const uint64_t psi = find_psi(q, n), ipsi = hinv(psi, q);
         std::vector<uint64_t> pw(n), ipw(n);
         pw[0] = 1;
         ipw[0] = 1;
+        const uint64_t psi_p = shoup(psi, q), ipsi_p = shoup(ipsi, q);
         for (uint32_t i = 1; i < n; i++) {
-            pw[i] = hmul(pw[i - 1], psi, q);
-            ipw[i] = hmul(ipw[i - 1], ipsi, q);
+            pw[i] = mul_shoup(pw[i - 1], psi, psi_p, q);
+            ipw[i] = mul_shoup(ipw[i - 1], ipsi, ipsi_p, q);
         }
         for (uint32_t i = 0; i < n; i++) {
             const uint32_t r = bitrev(i, c->L);
             tw[(size_t)l * n + i] = Tw{pw[r], shoup(pw[r], q)};
             itw[(size_t)l * n + i] = Tw{ipw[r], shoup(ipw[r], q)};
+            if (f64) {
+                twf[(size_t)l * n + i] = centred(pw[r], q, qinv);
+                twf[((size_t)c->K + l) * n + i] = centred(ipw[r], q, qinv);
+            }
         }
     }
 
@@ -807,6 +871,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     if (st == FHE_OK) st = alloc_copy(&c->d_pc, pc.data(), pc.size() * sizeof(PrimeConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_tw, tw.data(), tw.size() * sizeof(Tw));
     if (st == FHE_OK) st = alloc_copy(&c->d_itw, itw.data(), itw.size() * sizeof(Tw));
+    if (st == FHE_OK && f64) st = alloc_copy(&c->d_twf, twf.data(), twf.size() * sizeof(TwF));
     if (st == FHE_OK) st = alloc_copy(&c->d_cc, cc, sizeof(ConvConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_mrc_q, mq, sizeof(MrcConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_mrc_p, mp, sizeof(MrcConst));
@@ -848,6 +913,9 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     d.mrc_p = (const MrcConst *)c->d_mrc_p;
     d.fallback = (unsigned long long *)c->d_counters;
     d.mx = (const ConvMx *)c->d_mx;
+    d.f64 = f64 ? 1 : 0;
+    d.twf = (const TwF *)c->d_twf;
+    d.itwf = f64 ? d.twf + (size_t)c->K * n : nullptr;
     uint64_t qmin = c->primes[0], qmax = c->primes[0];
     for (uint32_t i = 1; i < k; i++) {
         qmin = c->primes[i] < qmin ? c->primes[i] : qmin;
@@ -867,6 +935,22 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     // lazy key switching also sums up to 16 products below 2q unreduced
     for (uint32_t i = 0; i < k; i++)
         if (c->primes[i] >= (1ull << 59)) d.lazy_q = 0;
+    // split transforms: the integer key switching sums operands below
+    // 4 (L + 1) q by column products, whose high halves must not overflow
+    c->split = split_ops((int)c->L);
+    c->relin_split_ok = c->split && (f64 || (d.lazy_q && qmax < (1ull << 58)));
+    if (c->split) {
+        // Integer fields: the fused kernels need a workgroup per row on every CU
+        // (256 rows of 16384, which fill a CU each); below that the split ones
+        // spread over the chip (n = 16384, products: 1 item 107 against 323 us,
+        // 8 items 284 against 344; 16 items 495 against 497; 32 items 862
+        // against 768).  Floating-point fields have no fused kernels and beat
+        // the integer ones at every size (n = 8192, 341 items: 2086 against
+        // 2562 us; n = 4096, 512 items: 931 against 1011).
+        const size_t full = f64 ? SIZE_MAX : (size_t)256 << (14 - c->L);
+        c->fused_min_rows[0] = c->fused_min_rows[1] = full;
+        c->relin_split_rows = full;
+    }
     // default chunk: about 8 GiB of product workspace
     size_t per = item_words_mul(c, false) * 8;
     c->default_limit = ((size_t)8 << 30) / per;
@@ -1575,11 +1659,15 @@ fhe_status fhe_bridge_to_bits(fhe_ctx *c, const uint64_t *rlk, const uint64_t *x
         uint64_t *C21 = D1 + gc * 3 * K * n;
         uint64_t *R1 = C21 + gc * k * n;
         uint64_t *gam = R1 + gc * 2 * k * n;
+        // the rest of the product workspace (T >= 3 products' worth per input)
+        uint64_t *free1 = gam + chains * 2 * K;
+        const size_t left1 = (size_t)((uint64_t *)ws2 + gmax * T * item_words_mul(c, true) - free1);
         FHE_TRY(run(c, KK_LIFT, st, [&] { return launch_lift(d, xg, xg, E1, 2, gc, st); }));
-        FHE_TRY(run(c, KK_SQUARE_TENSOR, st, [&] { return launch_square_tensor(d, xg, E1, D1, gc, st); }));
+        // the chains' rounding reads the lifted rows of E1 again
+        FHE_TRY(tensor_phase(c, xg, xg, E1, free1, D1, gc, st));
         FHE_TRY(run(c, KK_SCALE, st, [&] { return launch_scale(d, D1, nullptr, C21, gc, st, 2, 1); }));
         FHE_HIP(hipMemsetAsync(R1, 0, gc * 2 * k * n * sizeof(uint64_t), st));
-        FHE_TRY(run(c, KK_RELIN_FUSED, st, [&] { return launch_relin_fused(d, C21, rlk, R1, gc, st); }));
+        FHE_TRY(relin_phase(c, C21, rlk, R1, gc, free1, left1, st));
         FHE_TRY(run(c, KK_BRIDGE, st, [&] { return launch_bridge_gamma(d, xg, E1, gam, chains, Tc, c0, st); }));
         FHE_TRY(run(c, KK_SCALE, st,
                     [&] { return launch_scale_chain(d, D1, xg, E1, gam, R1, y, chains, Tc, st); }));

@@ -7,6 +7,7 @@
 #include "tables.hpp"
 
 struct Tw;
+struct TwF;
 
 // Everything a kernel needs to know about the context, passed by value.
 struct DevCtx {
@@ -23,6 +24,8 @@ struct DevCtx {
     int lazy_all;           // every prime of Q and P below 2^64 / (4 (L + 1)): lazy transforms
     uint64_t lazy_limbs;    // bit l: prime l (Q then P) below 2^64 / (4 (L + 1))
     int digit_raw;          // every Q prime below 4 min(Q): digits enter the lazy transforms as they are
+    int f64;                // every prime of Q and P below 2^50, n >= 4096: floating-point split transforms
+    const TwF *twf, *itwf;  // [K][n] their twiddles, or null
     const ConvMx *mx;       // matrix-core base conversion tables, or null (vector ALU conversions)
 };
 
@@ -41,6 +44,8 @@ enum KernelKind {
     KK_TENSOR_INTT,
     KK_PASS0_VALU,
     KK_PASS0_MFMA,
+    KK_SPLIT_TENSOR,
+    KK_SPLIT_RELIN,
     KK_COUNT
 };
 
@@ -51,6 +56,21 @@ enum NttMode {
     NTT_INV_MONT = 2,    // inverse, times n^-1 2^64 (after Montgomery products)
     NTT_FWD_NINVM = 3    // forward, then times n^-1 2^64 (relinearization key form)
 };
+
+// ---- product pipeline on the split transforms (kernels_split.hip), n = 4096, 8192, 16384 ----
+struct SplitOps {
+    // Transform phase of items products (a, b; squares of a): E [items][npoly][K][n]
+    // holds the lifted P rows, X (the same size; E itself where its P rows are
+    // not needed any more) receives the half-transformed rows, Dt
+    // [items][3][K][n] the tensor, canonical.
+    hipError_t (*tensor)(const DevCtx &, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X,
+                         uint64_t *Dt, bool square, size_t items, hipStream_t s);
+    // Key switching of C2 [items][k][n] added to out; ws: items (k^2 + 2k) n words.
+    hipError_t (*relin)(const DevCtx &, const uint64_t *C2, const uint64_t *rlk, uint64_t *ws, uint64_t *out,
+                        size_t items, hipStream_t s);
+};
+// The launches for ring degree 2^L, or null where there are none.
+const SplitOps *split_ops(int L);
 
 // ---- transforms (kernels_ntt.hip) ----
 // Launches of one ring degree (the launch_* functions below pick them by c.L).

@@ -914,6 +914,14 @@ const NttOps *ops(int L) {
 
 }  // namespace
 
+const SplitOps *split_ops_12();
+const SplitOps *split_ops_13();
+const SplitOps *split_ops_14();
+
+const SplitOps *split_ops(int L) {
+    return L == 12 ? split_ops_12() : L == 13 ? split_ops_13() : L == 14 ? split_ops_14() : nullptr;
+}
+
 hipError_t launch_ntt_rows(const DevCtx &c, uint64_t *data, size_t nrows, int kmod, int limb_off,
                            int mode, hipStream_t s) {
     const NttOps *o = ops(c.L);

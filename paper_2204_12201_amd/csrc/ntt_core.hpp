@@ -51,6 +51,11 @@ struct Geo {
 
 __device__ __forceinline__ uint32_t lds_pos(uint32_t idx) { return idx + (idx >> 4); }
 
+// Twiddle of the floating-point transforms (ntt_field.hpp): w centred modulo p, w / p.
+struct TwF {
+    double w, wi;
+};
+
 // Opaque copy of a value: index math derived from it is recomputed where it is
 // used instead of being kept live (as 16 addresses per row) across stages.
 __device__ __forceinline__ uint32_t fresh(uint32_t v) {
@@ -206,8 +211,8 @@ __device__ __forceinline__ void inv_pass(uint64_t (&x)[1 << LE], int tid, const 
     }
 }
 
-template <int L, int LE, int P>
-__device__ __forceinline__ void lds_store(uint64_t *lds, const uint64_t (&x)[1 << LE], int tid) {
+template <int L, int LE, int P, class V>
+__device__ __forceinline__ void lds_store(V *lds, const V (&x)[1 << LE], int tid) {
     constexpr int R = 1 << Geo<L, LE>::R(P), G = (1 << LE) / R;
 #pragma unroll
     for (int g = 0; g < G; g++)
@@ -215,8 +220,8 @@ __device__ __forceinline__ void lds_store(uint64_t *lds, const uint64_t (&x)[1 <
         for (int e = 0; e < R; e++) lds[lds_pos(elem_index<L, LE, P>(tid, g, e))] = x[g * R + e];
 }
 
-template <int L, int LE, int P>
-__device__ __forceinline__ void lds_load(const uint64_t *lds, uint64_t (&x)[1 << LE], int tid) {
+template <int L, int LE, int P, class V>
+__device__ __forceinline__ void lds_load(const V *lds, V (&x)[1 << LE], int tid) {
     constexpr int R = 1 << Geo<L, LE>::R(P), G = (1 << LE) / R;
 #pragma unroll
     for (int g = 0; g < G; g++)
@@ -230,8 +235,8 @@ __device__ __forceinline__ void lds_load(const uint64_t *lds, uint64_t (&x)[1 <<
 // previous exchange) and between the store and the load.  Otherwise the
 // exchange stays inside the wave, whose LDS operations execute in order, so
 // only the compiler is kept from reordering them.
-template <int L, int LE, int A, int B>
-__device__ __forceinline__ void exchange(uint64_t *lds, uint64_t (&x)[1 << LE], int tid) {
+template <int L, int LE, int A, int B, class V>
+__device__ __forceinline__ void exchange(V *lds, V (&x)[1 << LE], int tid) {
     constexpr bool block = (A == 0 || B == 0) && Geo<L, LE>::T > 64;
     if constexpr (block) {
         __syncthreads();
