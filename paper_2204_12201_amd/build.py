@@ -43,6 +43,7 @@ UNITS += [(s, os.path.splitext(s)[0], []) for s in
 EXTRA = {
     "kernels_conv.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "kernels_lin.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "kernels_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -384,9 +384,18 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
             return run(c, KK_SQUARE_TENSOR, s, [&] { return launch_square_tensor(d, a, E, Dt, items, s); });
         return run(c, KK_MUL_TENSOR, s, [&] { return launch_mul_tensor(d, a, b, E, Dt, items, s); });
     }
-    if (c->split) return run(c, KK_SPLIT_TENSOR, s, [&] { return c->split->tensor(d, a, b, E, X, Dt, square, items, s); });
+    if (c->split) {
+        FHE_TRY(run(c, KK_FWD_EXT, s, [&] { return c->split->fwd(d, a, b, E, X, square ? 2 : 4, items, s); }));
+        FHE_TRY(run(c, KK_SPLIT_TENSOR, s, [&] { return c->split->blocks(d, X, Dt, square, items, s); }));
+        return run(c, KK_TENSOR_INTT, s, [&] { return c->split->inv(d, Dt, items, s); });
+    }
     FHE_TRY(run(c, KK_FWD_EXT, s, [&] { return launch_fwd_ext(d, a, b, E, square ? 2 : 4, items, s); }));
     return run(c, KK_TENSOR_INTT, s, [&] { return launch_tensor_intt(d, E, Dt, square, items, s); });
+}
+
+// Whether key switching of `items` ciphertexts takes the split kernels.
+bool relin_is_split(const fhe_ctx *c, size_t items) {
+    return c->relin_split_ok && items * c->k < c->relin_split_rows;
 }
 
 // Key switching of C2 [items][k][n] added to out.  scratch: `words` words that
@@ -394,10 +403,31 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
 fhe_status relin_phase(fhe_ctx *c, const uint64_t *C2, const uint64_t *rlk, uint64_t *out, size_t items,
                        uint64_t *scratch, size_t words, hipStream_t s) {
     const DevCtx &d = c->dev;
-    const size_t k = c->k;
-    if (c->relin_split_ok && items * k < c->relin_split_rows && items * (k * k + 2 * k) * c->n <= words)
-        return run(c, KK_SPLIT_RELIN, s, [&] { return c->split->relin(d, C2, rlk, scratch, out, items, s); });
+    const size_t k = c->k, n = c->n;
+    if (relin_is_split(c, items) && items * (k * k + 2 * k) * n <= words) {
+        uint64_t *R = scratch + items * k * k * n;
+        FHE_TRY(run(c, KK_FWD_EXT, s, [&] { return c->split->digits(d, C2, scratch, items, s); }));
+        return run(c, KK_SPLIT_RELIN, s, [&] { return c->split->relin(d, scratch, rlk, R, out, items, s); });
+    }
     return run(c, KK_RELIN_FUSED, s, [&] { return launch_relin_fused(d, C2, rlk, out, items, s); });
+}
+
+// A batch of products on the split transforms with the conversions fused into
+// the column kernels (matrix-core conversions); E, Dt, C2 as in mul_relin_impl.
+fhe_status split_products(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, const uint64_t *b, uint64_t *out,
+                          uint64_t *E, uint64_t *Dt, uint64_t *C2, size_t items, bool relin, hipStream_t s) {
+    const DevCtx &d = c->dev;
+    const bool square = (a == b);
+    const size_t n = c->n, K = c->K, k = c->k, npoly = square ? 2 : 4;
+    FHE_TRY(run(c, KK_LIFT, s, [&] { return c->split->lift_fwd(d, a, b, E, (int)npoly, items, s); }));
+    FHE_TRY(run(c, KK_SPLIT_TENSOR, s, [&] { return c->split->blocks(d, E, Dt, square, items, s); }));
+    // the digits go to E, whose rows the tensor has read, while Dt is read; the
+    // key-switching rows then to Dt
+    const bool direct = relin && relin_is_split(c, items) && k * k <= npoly * K;
+    uint64_t *D = direct ? E : nullptr;
+    FHE_TRY(run(c, KK_SCALE, s, [&] { return c->split->inv_scale(d, Dt, out, C2, D, items, s); }));
+    if (direct) return run(c, KK_SPLIT_RELIN, s, [&] { return c->split->relin(d, D, rlk, Dt, out, items, s); });
+    return relin ? relin_phase(c, C2, rlk, out, items, E, items * (npoly + 3) * K * n, s) : FHE_OK;
 }
 
 // The product pipeline on `count` items with workspace for min(count, limit).
@@ -417,6 +447,10 @@ fhe_status mul_relin_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, co
         uint64_t *Dt = E + items * npoly * K * n;
         uint64_t *C2 = Dt + items * 3 * K * n;
         const DevCtx &d = c->dev;
+        if (c->split && d.mx && items * K < c->fused_min_rows[square ? 1 : 0]) {
+            FHE_TRY(split_products(c, rlk, ai, bi, oi, E, Dt, C2, items, relin, s));
+            continue;
+        }
         FHE_TRY(run(c, KK_LIFT, s, [&] { return launch_lift(d, ai, bi, E, npoly, items, s); }));
         FHE_TRY(tensor_phase(c, ai, bi, E, E, Dt, items, s));
         FHE_TRY(run(c, KK_SCALE, s, [&] { return launch_scale(d, Dt, oi, C2, items, s); }));
@@ -923,8 +957,9 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     }
     d.digit_raw = (u128)qmax < (u128)qmin * 4;
     d.lazy_q = d.lazy_all = 1;
-    d.lazy_limbs = 0;
+    d.lazy_limbs = d.big_limbs = 0;
     for (uint32_t i = 0; i < c->K; i++) {
+        if (c->primes[i] >= (1ull << 47)) d.big_limbs |= 1ull << i;
         if (c->primes[i] < UINT64_MAX / (4ull * (c->L + 1))) {
             d.lazy_limbs |= 1ull << i;
         } else {

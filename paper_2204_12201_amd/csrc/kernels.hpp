@@ -25,6 +25,7 @@ struct DevCtx {
     uint64_t lazy_limbs;    // bit l: prime l (Q then P) below 2^64 / (4 (L + 1))
     int digit_raw;          // every Q prime below 4 min(Q): digits enter the lazy transforms as they are
     int f64;                // every prime of Q and P below 2^50, n >= 4096: floating-point split transforms
+    uint64_t big_limbs;     // bit l: prime l is at least 2^47 (FieldF<true>)
     const TwF *twf, *itwf;  // [K][n] their twiddles, or null
     const ConvMx *mx;       // matrix-core base conversion tables, or null (vector ALU conversions)
 };
@@ -58,15 +59,26 @@ enum NttMode {
 };
 
 // ---- product pipeline on the split transforms (kernels_split.hip), n = 4096, 8192, 16384 ----
+// Rows between two of these launches hold half-transformed field values.
 struct SplitOps {
-    // Transform phase of items products (a, b; squares of a): E [items][npoly][K][n]
-    // holds the lifted P rows, X (the same size; E itself where its P rows are
-    // not needed any more) receives the half-transformed rows, Dt
-    // [items][3][K][n] the tensor, canonical.
-    hipError_t (*tensor)(const DevCtx &, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X,
-                         uint64_t *Dt, bool square, size_t items, hipStream_t s);
-    // Key switching of C2 [items][k][n] added to out; ws: items (k^2 + 2k) n words.
-    hipError_t (*relin)(const DevCtx &, const uint64_t *C2, const uint64_t *rlk, uint64_t *ws, uint64_t *out,
+    // X [items][npoly][K][n]: lift of a (and b) and pass 0 (c.mx only)
+    hipError_t (*lift_fwd)(const DevCtx &, const uint64_t *a, const uint64_t *b, uint64_t *X, int npoly, size_t items,
+                           hipStream_t s);
+    // the same from rows lifted to E (P rows; X may be E)
+    hipError_t (*fwd)(const DevCtx &, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X, int npoly,
+                      size_t items, hipStream_t s);
+    // Dt [items][3][K][n]: tensor of X
+    hipError_t (*blocks)(const DevCtx &, const uint64_t *X, uint64_t *Dt, bool square, size_t items, hipStream_t s);
+    // Dt finished in place, canonical
+    hipError_t (*inv)(const DevCtx &, uint64_t *Dt, size_t items, hipStream_t s);
+    // Dt finished, scaled and rounded: components 0, 1 to out; component 2 to D
+    // [items][k][k][n] as half-transformed digits, or to C2 where D is null (c.mx only)
+    hipError_t (*inv_scale)(const DevCtx &, const uint64_t *Dt, uint64_t *out, uint64_t *C2, uint64_t *D, size_t items,
+                            hipStream_t s);
+    // D from C2 [items][k][n]
+    hipError_t (*digits)(const DevCtx &, const uint64_t *C2, uint64_t *D, size_t items, hipStream_t s);
+    // key switching of D added to out; R: items 2k n words
+    hipError_t (*relin)(const DevCtx &, const uint64_t *D, const uint64_t *rlk, uint64_t *R, uint64_t *out,
                         size_t items, hipStream_t s);
 };
 // The launches for ring degree 2^L, or null where there are none.

@@ -3,6 +3,9 @@
 // kernels run the other passes of 1024 consecutive residues in one wave.
 // Rows between the two halves hold field values (lazy integers or doubles).
 //
+//  k_col_lift      lift of the inputs and pass 0 of their forward transforms
+//  k_col_scale     pass 0 of the inverse of the tensor rows, scale-and-round, and
+//                  pass 0 of the digits
 //  k_split_fwd     pass 0 of the extended inputs
 //  k_split_tensor  blocks: forward, tensor product, inverse
 //  k_split_inv     pass 0 of the inverse of the tensor rows, canonical
@@ -14,6 +17,7 @@
 // One object per ring degree 2^FHE_NTT_L.
 #include <type_traits>
 
+#include "conv_mx.hpp"
 #include "kernels.hpp"
 #include "modarith.hpp"
 #include "ntt_core.hpp"
@@ -27,6 +31,209 @@ constexpr int kBlkWords = 1088;  // LDS words of one wave's block (1024 plus pad
 template <int L>
 constexpr int col_groups() {
     return Geo<L>::T / kColThreads;
+}
+
+// ---- column kernels fused with the base conversions ----------------------------
+// A workgroup of W waves owns C columns: the 16 C coefficients c0 + [0, C) + e
+// n/16, e = 0..15.  The conversions need every residue of a coefficient, pass 0
+// the 16 residues of a column modulo one prime: they meet in LDS
+// (rows[limb][e][C]), so the lifted and the inverse transformed rows never go
+// through memory.  Bases of at most 8 primes a side (ConvMx).
+
+template <int C, int NT>
+struct ColShared {
+    MxSharedT<NT, 16 * C> mx;
+    uint64_t rows[1][16][C];  // [limbs], dynamic
+};
+
+// Calls fn(unit, column, field) for the units 0 .. count - 1 of the workgroup's
+// waves: 64 / C units side by side in the lanes of a wave, unit u with the
+// field of prime limb(u).
+template <class F, int C, int W, class Limb, class Fn>
+__device__ __forceinline__ void col_units(const DevCtx &c, int first, int step, int count, const Limb &limb,
+                                          const Fn &fn) {
+    const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (C == 64) {
+        for (int u = first + step * w; u < count; u += step * W)
+            F::with(c, limb(u), [&](const auto &f) { fn(u, lane, f); });
+    } else {
+        constexpr int S = 64 / C;
+        for (int u = first + step * (w * S + lane / C); u < count; u += step * W * S)
+            F::with_lanes(c, limb(u), [&](const auto &f) { fn(u, lane % C, f); });
+    }
+}
+
+// Lift of the inputs and pass 0 of their forward transforms: grid (n/16/C,
+// npoly, items).  The Q rows go straight through pass 0, the lifted P rows
+// through LDS.
+template <int L, class F, int C, int W>
+__global__ __launch_bounds__(64 * W) void k_col_lift(DevCtx c, const uint64_t *__restrict__ a,
+                                                     const uint64_t *__restrict__ b, uint64_t *__restrict__ X,
+                                                     int npoly) {
+    constexpr int n = Geo<L>::N, T = Geo<L>::T;
+    extern __shared__ uint64_t shared_words[];
+    ColShared<C, 1> &sh = *(ColShared<C, 1> *)shared_words;
+    const int k = c.k, kp = c.kp, K = c.K, poly = (int)blockIdx.y, c0 = (int)blockIdx.x * C;
+    const size_t item = blockIdx.z;
+    const uint64_t *src = poly < 2 ? a + (item * 2 + poly) * (size_t)k * n : b + (item * 2 + poly - 2) * (size_t)k * n;
+    uint64_t *dst = X + (item * npoly + poly) * (size_t)K * n;
+    const uint32_t lane = threadIdx.x & 63u, col = lane & 15u, g = lane >> 4;
+    const int w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    mx_stage_table(sh.mx, 0, c.mx->a_lift);
+    mx_stage_lift_slots(sh.mx, c);
+    if (threadIdx.x == 0) sh.mx.count = 0;
+    __syncthreads();
+    const int a16 = (int)((lane ^ 16u) << 2), a32 = (int)((lane ^ 32u) << 2);
+    uint32_t rq[2];
+    bool jv[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        rq[h] = mx_row((int)g + 4 * h, k, 0, n);
+        jv[h] = (int)g + 4 * h < kp;
+    }
+    for (int t = w; t < C; t += W) {  // tile: stride e, 16 columns
+        const int e = t / (C / 16), cc = t % (C / 16) * 16 + (int)col;
+        const uint64_t *s0 = src + e * T + c0 + cc;
+        uint64_t x[2] = {s0[rq[0]], s0[rq[1]]}, r[2];
+        if (mx_lift_tile(sh.mx, lane, a16, a32, x, r)) {
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+                if (jv[h]) sh.rows[g + 4 * h][e][cc] = r[h];
+        } else if (g == 0) {
+            sh.mx.item[atomicAdd(&sh.mx.count, 1)] = e * C + cc;
+        }
+    }
+    auto limb_q = [](int l) { return l; };
+    col_units<F, C, W>(c, 0, 1, k, limb_q, [&](int l, int cl, const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        typename Fd::V x[1][16];
+        const uint64_t *row = src + (size_t)l * n + c0 + cl;
+#pragma unroll
+        for (int s = 0; s < 16; s++) x[0][s] = f.in(row[s * T]);
+        fwd_pass_t<L, 0, 1>(x, 0, f, TwGlobal<typename Fd::T>{f.tw});
+        uint64_t *o = dst + (size_t)l * n + c0 + cl;
+#pragma unroll
+        for (int s = 0; s < 16; s++) o[s * T] = Fd::to_bits(x[0][s]);
+    });
+    __syncthreads();
+    const int cnt = sh.mx.count;
+    if (cnt) {  // the same in the whole workgroup
+        for (int i = (int)threadIdx.x; i < cnt; i += 64 * W) {
+            const int e = sh.mx.item[i] / C, cc = sh.mx.item[i] % C;
+            uint64_t xa[FHE_MX_MAXB];
+#pragma unroll
+            for (int l = 0; l < FHE_MX_MAXB; l++) xa[l] = l < k ? src[(size_t)l * n + e * T + c0 + cc] : 0;
+            lift_exact<FHE_MX_MAXB, FHE_MX_MAXB, false>(c, xa, [&](int j, uint64_t r) { sh.rows[j][e][cc] = r; });
+        }
+        __syncthreads();
+    }
+    auto limb_p = [k](int l) { return k + l; };
+    col_units<F, C, W>(c, 0, 1, kp, limb_p, [&](int l, int cl, const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        typename Fd::V x[1][16];
+#pragma unroll
+        for (int s = 0; s < 16; s++) x[0][s] = f.in(sh.rows[l][s][cl]);
+        fwd_pass_t<L, 0, 1>(x, 0, f, TwGlobal<typename Fd::T>{f.tw});
+        uint64_t *o = dst + (size_t)(k + l) * n + c0 + cl;
+#pragma unroll
+        for (int s = 0; s < 16; s++) o[s * T] = Fd::to_bits(x[0][s]);
+    });
+}
+
+// Pass 0 of the inverse transforms of the tensor rows, scale-and-round, and
+// pass 0 of the digits: grid (n/16/C, 2 + J, items).  blockIdx.y 0, 1:
+// components 0, 1 into out.  2 + p: component 2 (computed by each of the J
+// parts), whose digits p, p + J, ... of the k^2 (digit, prime) pairs go to D
+// [item][digit][prime] (field DF of the key switching); D null: the component itself to C2 (J = 1).
+template <int L, class F, class DF, bool RAW, int C, int W>
+__global__ __launch_bounds__(64 * W) void k_col_scale(DevCtx c, const uint64_t *__restrict__ Dt,
+                                                      uint64_t *__restrict__ out, uint64_t *__restrict__ C2,
+                                                      uint64_t *__restrict__ D, int J) {
+    constexpr int n = Geo<L>::N, T = Geo<L>::T;
+    extern __shared__ uint64_t shared_words[];
+    ColShared<C, 3> &sh = *(ColShared<C, 3> *)shared_words;
+    const int k = c.k, kp = c.kp, K = c.K, c0 = (int)blockIdx.x * C;
+    const int comp = blockIdx.y < 2 ? (int)blockIdx.y : 2, part = (int)blockIdx.y - 2;
+    const size_t item = blockIdx.z;
+    const uint64_t *src = Dt + (item * 3 + comp) * (size_t)K * n + c0;
+    uint64_t *dst = (comp < 2 ? out + (item * 2 + comp) * (size_t)k * n : C2 + item * (size_t)k * n) + c0;
+    const bool digits = comp == 2 && D;
+    const uint32_t lane = threadIdx.x & 63u, col = lane & 15u, g = lane >> 4;
+    const int w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    mx_stage_table(sh.mx, 0, c.mx->a_scale);
+    mx_stage_table(sh.mx, 1, c.mx->a_p2q);
+    mx_stage_table(sh.mx, 2, c.mx->a_sdp);
+    mx_stage_scale_slots(sh.mx, c);
+    if (threadIdx.x == 0) sh.mx.count = 0;
+    col_units<F, C, W>(c, 0, 1, K, [](int l) { return l; }, [&](int l, int cl, const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        typename Fd::V x[1][16];
+        const uint64_t *row = src + (size_t)l * n + cl;
+#pragma unroll
+        for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(row[s * T]);
+        inv_pass_t<L, 0, 1>(x, 0, f, TwGlobal<typename Fd::T>{f.itw});
+#pragma unroll
+        for (int s = 0; s < 16; s++) sh.rows[l][s][cl] = f.tensor_out(x[0][s]);
+    });
+    __syncthreads();
+    const int a16 = (int)((lane ^ 16u) << 2), a32 = (int)((lane ^ 32u) << 2);
+    int sq[2], sp[2];
+    bool iv[2], jv[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int s = (int)g + 4 * h;
+        iv[h] = s < k;
+        jv[h] = s < kp;
+        sq[h] = s < k ? s : k - 1;  // absent primes read a present row (their constants are zero)
+        sp[h] = k + (s < kp ? s : kp - 1);
+    }
+    for (int t = w; t < C; t += W) {
+        const int e = t / (C / 16), cc = t % (C / 16) * 16 + (int)col;
+        const uint64_t dq[2] = {sh.rows[sq[0]][e][cc], sh.rows[sq[1]][e][cc]};
+        const uint64_t dp[2] = {sh.rows[sp[0]][e][cc], sh.rows[sp[1]][e][cc]};
+        uint64_t r[2];
+        if (mx_scale_tile(sh.mx, lane, a16, a32, dq, dp, jv, r)) {
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                if (iv[h]) {
+                    // a tile's words are read by this wave alone, before it writes them
+                    if (digits) sh.rows[g + 4 * h][e][cc] = r[h];
+                    else dst[(size_t)(g + 4 * h) * n + e * T + cc] = r[h];
+                }
+            }
+        } else if (g == 0) {
+            sh.mx.item[atomicAdd(&sh.mx.count, 1)] = e * C + cc;
+        }
+    }
+    __syncthreads();
+    const int cnt = sh.mx.count;
+    if (cnt) {
+        for (int i = (int)threadIdx.x; i < cnt; i += 64 * W) {
+            const int e = sh.mx.item[i] / C, cc = sh.mx.item[i] % C;
+            uint64_t dqa[FHE_MX_MAXB], dpa[FHE_MX_MAXB];
+#pragma unroll
+            for (int l = 0; l < FHE_MX_MAXB; l++) {
+                dqa[l] = l < k ? sh.rows[l][e][cc] : 0;
+                dpa[l] = l < kp ? sh.rows[k + l][e][cc] : 0;
+            }
+            scale_exact<FHE_MX_MAXB, FHE_MX_MAXB, false>(c, dqa, dpa, [&](int l, uint64_t r) {
+                if (digits) sh.rows[l][e][cc] = r;
+                else dst[(size_t)l * n + e * T + cc] = r;
+            });
+        }
+        __syncthreads();
+    }
+    if (!digits) return;
+    col_units<DF, C, W>(c, part, J, k * k, [k](int u) { return u % k; }, [&](int u, int cl, const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        typename Fd::V x[1][16];
+#pragma unroll
+        for (int s = 0; s < 16; s++) x[0][s] = f.template digit<RAW>(sh.rows[u / k][s][cl]);
+        fwd_pass_t<L, 0, 1>(x, 0, f, TwGlobal<typename Fd::T>{f.tw});
+        uint64_t *o = D + (item * k * k + u) * (size_t)n + c0 + cl;
+#pragma unroll
+        for (int s = 0; s < 16; s++) o[s * T] = Fd::to_bits(x[0][s]);
+    });
 }
 
 // grid (column groups, K npoly, items)
@@ -44,11 +251,14 @@ __global__ __launch_bounds__(kColThreads) void k_split_fwd(DevCtx c, const uint6
     const uint64_t *src = limb < k ? (poly < 2 ? a + ((item * 2 + poly) * k + limb) * (size_t)n
                                                : b + ((item * 2 + poly - 2) * k + limb) * (size_t)n)
                                    : E + row;
+    uint64_t v[16];  // in flight while the prime's constants are fetched
+#pragma unroll
+    for (int s = 0; s < 16; s++) v[s] = src[natural_index<L>(tid, s)];
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         typename Fd::V x[1][16];
 #pragma unroll
-        for (int s = 0; s < 16; s++) x[0][s] = f.in(src[natural_index<L>(tid, s)]);
+        for (int s = 0; s < 16; s++) x[0][s] = f.in(v[s]);
         fwd_pass_t<L, 0, 1>(x, (int)tid, f, TwGlobal<typename Fd::T>{f.tw});
 #pragma unroll
         for (int s = 0; s < 16; s++) dst[natural_index<L>(tid, s)] = Fd::to_bits(x[0][s]);
@@ -137,11 +347,18 @@ __global__ __launch_bounds__(256) void k_split_tensor(DevCtx c, const uint64_t *
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     const uint32_t tid = 64u * blk + lane;
     const size_t item = blockIdx.y;
+    uint64_t raw[16];  // in flight while the prime's constants are fetched
+    if (w < NP) {
+        const uint64_t *row = X + ((item * NP + w) * K + limb) * (size_t)n;
+#pragma unroll
+        for (int s = 0; s < 16; s++) raw[s] = row[elem_index<L, 4, 1>(tid, 0, s)];
+    }
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         V x[1][16];
         if (w < NP) {
-            load_block<L, Fd>(x[0], X + ((item * NP + w) * K + limb) * (size_t)n, tid);
+#pragma unroll
+            for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(raw[s]);
             f.enter_block(x);
             fwd_block<L, 1, 1>(x, lds[w], lane, (int)tid, f, TW{f.tw});
             f.operands(x);
@@ -204,11 +421,14 @@ __global__ __launch_bounds__(kColThreads) void k_split_inv(DevCtx c, uint64_t *_
     const uint32_t tid = blockIdx.x * kColThreads + threadIdx.x;
     const int K = c.K, limb = (int)blockIdx.y % K;
     uint64_t *row = Dt + ((size_t)blockIdx.z * 3 * K + blockIdx.y) * (size_t)n;
+    uint64_t v[16];
+#pragma unroll
+    for (int s = 0; s < 16; s++) v[s] = row[natural_index<L>(tid, s)];
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         typename Fd::V x[1][16];
 #pragma unroll
-        for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(row[natural_index<L>(tid, s)]);
+        for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(v[s]);
         inv_pass_t<L, 0, 1>(x, (int)tid, f, TwGlobal<typename Fd::T>{f.itw});
 #pragma unroll
         for (int s = 0; s < 16; s++) row[natural_index<L>(tid, s)] = f.tensor_out(x[0][s]);
@@ -395,17 +615,21 @@ __global__ __launch_bounds__(kColThreads) void k_split_fin(DevCtx c, const uint6
     const int k = c.k, limb = (int)blockIdx.y % k;
     const size_t o = ((size_t)blockIdx.z * 2 * k + blockIdx.y) * (size_t)n;
     const uint64_t q = c.pc[limb].q;
+    // both inputs in flight while the prime's constants are fetched
+    uint64_t v[16], a[16];
+#pragma unroll
+    for (int s = 0; s < 16; s++) v[s] = R[o + natural_index<L>(tid, s)];
+#pragma unroll
+    for (int s = 0; s < 16; s++) a[s] = out[o + natural_index<L>(tid, s)];
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         typename Fd::V x[1][16];
 #pragma unroll
-        for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(R[o + natural_index<L>(tid, s)]);
+        for (int s = 0; s < 16; s++) x[0][s] = Fd::from_bits(v[s]);
         inv_pass_t<L, 0, 1>(x, (int)tid, f, TwGlobal<typename Fd::T>{f.itw});
 #pragma unroll
-        for (int s = 0; s < 16; s++) {
-            const size_t i = o + natural_index<L>(tid, s);
-            out[i] = add_mod(f.relin_out(x[0][s]), out[i], q);
-        }
+        for (int s = 0; s < 16; s++)
+            out[o + natural_index<L>(tid, s)] = add_mod(f.relin_out(x[0][s]), a[s], q);
     });
 }
 
@@ -424,78 +648,139 @@ dim3 many_grid(size_t cols, size_t items) {
     return dim3((unsigned)cols, (unsigned)(fit < most ? fit : most));
 }
 
-template <int L, class F>
-hipError_t split_tensor_f(const DevCtx &c, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X,
-                          uint64_t *Dt, bool sq, size_t items, hipStream_t s) {
-    constexpr unsigned CG = col_groups<L>(), NB = Geo<L>::N / 1024;
-    const int npoly = sq ? 2 : 4;
-    hipLaunchKernelGGL((k_split_fwd<L, F>), dim3(CG, c.K * npoly, (unsigned)items), dim3(kColThreads), 0, s, c, a, b, E,
-                       X, npoly);
-    if (items * c.K * NB <= kFewBlocks) {
-        const dim3 grid(c.K * NB, (unsigned)items);
-        if (sq) hipLaunchKernelGGL((k_split_tensor<L, F, true>), grid, dim3(192), 0, s, c, X, Dt);
-        else hipLaunchKernelGGL((k_split_tensor<L, F, false>), grid, dim3(256), 0, s, c, X, Dt);
-    } else if (sq) {
-        constexpr int W = 12;
-        hipLaunchKernelGGL((k_split_tensor_many<L, F, true, W>), many_grid<W>(c.K * NB, items), dim3(64 * W), 0, s, c,
-                           X, Dt, items);
-    } else {
-        constexpr int W = 12;
-        hipLaunchKernelGGL((k_split_tensor_many<L, F, false, W>), many_grid<W>(c.K * NB, items), dim3(64 * W), 0, s, c,
-                           X, Dt, items);
-    }
-    hipLaunchKernelGGL((k_split_inv<L, F>), dim3(CG, 3 * c.K, (unsigned)items), dim3(kColThreads), 0, s, c, Dt);
-    return hipGetLastError();
-}
+// ---- launches --------------------------------------------------------------------
 
 template <int L>
-hipError_t split_tensor(const DevCtx &c, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X,
-                        uint64_t *Dt, bool sq, size_t items, hipStream_t s) {
-    if (c.f64) return split_tensor_f<L, FamF>(c, a, b, E, X, Dt, sq, items, s);
-    if (c.lazy_all) return split_tensor_f<L, FamU<true>>(c, a, b, E, X, Dt, sq, items, s);
-    return split_tensor_f<L, FamU<false>>(c, a, b, E, X, Dt, sq, items, s);
-}
+struct SplitL {
+    static constexpr unsigned CG = col_groups<L>(), NB = Geo<L>::N / 1024;
 
-template <int L, class F, bool RAW>
-hipError_t split_relin_f(const DevCtx &c, const uint64_t *C2, const uint64_t *rlk, uint64_t *ws, uint64_t *out,
-                         size_t items, hipStream_t s) {
-    constexpr unsigned CG = col_groups<L>(), NB = Geo<L>::N / 1024;
-    const size_t k = c.k;
-    uint64_t *D = ws, *R = ws + items * k * k * Geo<L>::N;
-    // few items: one thread group per (digit, prime), and the digits of a block
-    // spread over waves; many: one pass over C2, one wave per block
-    const size_t waves = items * k * NB;
-    const int jper = items * k * k * CG <= 1024 ? 1 : (int)k;
-    const unsigned parts = (unsigned)((k + jper - 1) / jper);
-    hipLaunchKernelGGL((k_split_digits<L, F, RAW>), dim3(CG, (unsigned)k * parts, (unsigned)items), dim3(kColThreads),
-                       0, s, c, C2, D, jper);
-    if (waves <= kFewBlocks / 2) {
-        const unsigned W = k < 8 ? (k < 2 ? 2 : (unsigned)k) : 8;
-        hipLaunchKernelGGL((k_split_relin<L, F>), dim3((unsigned)k * NB, (unsigned)items), dim3(64 * W),
-                           (W * kBlkWords + 2048) * 8, s, c, D, rlk, R);
-    } else {
-        constexpr int W = 12;
-        hipLaunchKernelGGL((k_split_relin_many<L, F, W>), many_grid<W>(k * NB, items), dim3(64 * W), 0, s, c, D, rlk,
-                           R, items);
+    // fn(field family of the tensor rows)
+    template <class Fn>
+    static hipError_t tensor_field(const DevCtx &c, const Fn &fn) {
+        if (c.f64) fn(FamF());
+        else if (c.lazy_all) fn(FamU<true>());
+        else fn(FamU<false>());
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_split_fin<L, F>), dim3(CG, 2 * (unsigned)k, (unsigned)items), dim3(kColThreads), 0, s, c, R,
-                       out);
-    return hipGetLastError();
-}
+    // fn(field family of key switching, digits enter as they are)
+    template <class Fn>
+    static hipError_t digit_field(const DevCtx &c, const Fn &fn) {
+        if (c.f64) fn(FamF(), std::false_type());
+        else if (c.digit_raw) fn(FamU<true>(), std::true_type());
+        else fn(FamU<true>(), std::false_type());
+        return hipGetLastError();
+    }
 
-template <int L>
-hipError_t split_relin(const DevCtx &c, const uint64_t *C2, const uint64_t *rlk, uint64_t *ws, uint64_t *out,
-                       size_t items, hipStream_t s) {
-    if (c.f64) return split_relin_f<L, FamF, false>(c, C2, rlk, ws, out, items, s);
-    if (c.digit_raw) return split_relin_f<L, FamU<true>, true>(c, C2, rlk, ws, out, items, s);
-    return split_relin_f<L, FamU<true>, false>(c, C2, rlk, ws, out, items, s);
-}
+    static hipError_t fwd(const DevCtx &c, const uint64_t *a, const uint64_t *b, const uint64_t *E, uint64_t *X,
+                          int npoly, size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            hipLaunchKernelGGL((k_split_fwd<L, decltype(fam)>), dim3(CG, c.K * npoly, (unsigned)items),
+                               dim3(kColThreads), 0, s, c, a, b, E, X, npoly);
+        });
+    }
+    static hipError_t blocks(const DevCtx &c, const uint64_t *X, uint64_t *Dt, bool sq, size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            typedef decltype(fam) F;
+            constexpr int W = 12;
+            if (items * c.K * NB <= kFewBlocks) {
+                const dim3 grid(c.K * NB, (unsigned)items);
+                if (sq) hipLaunchKernelGGL((k_split_tensor<L, F, true>), grid, dim3(192), 0, s, c, X, Dt);
+                else hipLaunchKernelGGL((k_split_tensor<L, F, false>), grid, dim3(256), 0, s, c, X, Dt);
+            } else if (sq) {
+                hipLaunchKernelGGL((k_split_tensor_many<L, F, true, W>), many_grid<W>(c.K * NB, items), dim3(64 * W),
+                                   0, s, c, X, Dt, items);
+            } else {
+                hipLaunchKernelGGL((k_split_tensor_many<L, F, false, W>), many_grid<W>(c.K * NB, items), dim3(64 * W),
+                                   0, s, c, X, Dt, items);
+            }
+        });
+    }
+    static hipError_t inv(const DevCtx &c, uint64_t *Dt, size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            hipLaunchKernelGGL((k_split_inv<L, decltype(fam)>), dim3(CG, 3 * c.K, (unsigned)items), dim3(kColThreads),
+                               0, s, c, Dt);
+        });
+    }
+    static hipError_t digits(const DevCtx &c, const uint64_t *C2, uint64_t *D, size_t items, hipStream_t s) {
+        // few items: one thread group per (digit, prime); many: one pass over C2
+        const size_t k = c.k;
+        const int jper = items * k * k * CG <= 1024 ? 1 : (int)k;
+        const unsigned parts = (unsigned)((k + jper - 1) / jper);
+        return digit_field(c, [&](auto fam, auto raw) {
+            hipLaunchKernelGGL((k_split_digits<L, decltype(fam), decltype(raw)::value>),
+                               dim3(CG, (unsigned)k * parts, (unsigned)items), dim3(kColThreads), 0, s, c, C2, D,
+                               jper);
+        });
+    }
+    static hipError_t relin(const DevCtx &c, const uint64_t *D, const uint64_t *rlk, uint64_t *R, uint64_t *out,
+                            size_t items, hipStream_t s) {
+        const size_t k = c.k;
+        return digit_field(c, [&](auto fam, auto) {
+            typedef decltype(fam) F;
+            constexpr int WM = 12;
+            if (items * k * NB <= kFewBlocks / 2) {
+                const unsigned W = k < 8 ? (k < 2 ? 2 : (unsigned)k) : 8;
+                hipLaunchKernelGGL((k_split_relin<L, F>), dim3((unsigned)k * NB, (unsigned)items), dim3(64 * W),
+                                   (W * kBlkWords + 2048) * 8, s, c, D, rlk, R);
+            } else {
+                hipLaunchKernelGGL((k_split_relin_many<L, F, WM>), many_grid<WM>(k * NB, items), dim3(64 * WM), 0, s,
+                                   c, D, rlk, R, items);
+            }
+            hipLaunchKernelGGL((k_split_fin<L, F>), dim3(CG, 2 * (unsigned)k, (unsigned)items), dim3(kColThreads), 0,
+                               s, c, R, out);
+        });
+    }
+
+    // Columns per workgroup of the fused column kernels: 64 fill the lanes of
+    // the pass-0 parts; 32 where 64 would leave one workgroup per CU (more than
+    // 8 rows in LDS), which cannot overlap its loads with its arithmetic; 16 (and
+    // 16 waves) for launches too small to fill the chip.
+    template <int C, int W, int NT, class Kern, class... A>
+    static void launch_col(Kern kern, const DevCtx &c, int limbs, unsigned y, size_t items, hipStream_t s, A... args) {
+        const size_t lds = sizeof(ColShared<C, NT>) + (size_t)(limbs - 1) * 16 * C * 8;
+        hipLaunchKernelGGL(kern, dim3(Geo<L>::T / C, y, (unsigned)items), dim3(64 * W), lds, s, c, args...);
+    }
+    static hipError_t lift_fwd(const DevCtx &c, const uint64_t *a, const uint64_t *b, uint64_t *X, int npoly,
+                               size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            typedef decltype(fam) F;
+            if (npoly * items * (Geo<L>::T / 64) <= 128)
+                launch_col<16, 8, 1>(k_col_lift<L, F, 16, 8>, c, c.kp, npoly, items, s, a, b, X, npoly);
+            else
+                launch_col<64, 8, 1>(k_col_lift<L, F, 64, 8>, c, c.kp, npoly, items, s, a, b, X, npoly);
+        });
+    }
+    static hipError_t inv_scale(const DevCtx &c, const uint64_t *Dt, uint64_t *out, uint64_t *C2, uint64_t *D,
+                                size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            typedef decltype(fam) F;
+            (void)digit_field(c, [&](auto dfam, auto raw) {
+                typedef decltype(dfam) DF;
+                constexpr bool RAW = decltype(raw)::value;
+                if constexpr (std::is_same<F, FamF>::value == std::is_same<DF, FamF>::value) {
+                    if (3 * items * (Geo<L>::T / 64) <= 128) {
+                        const int J = D && c.k > 3 ? 4 : 1;
+                        launch_col<16, 8, 3>(k_col_scale<L, F, DF, RAW, 16, 8>, c, c.K, 2 + J, items, s, Dt, out, C2,
+                                              D, J);
+                    } else if (c.K <= 8) {
+                        launch_col<64, 8, 3>(k_col_scale<L, F, DF, RAW, 64, 8>, c, c.K, 3, items, s, Dt, out, C2, D,
+                                             1);
+                    } else {
+                        launch_col<32, 8, 3>(k_col_scale<L, F, DF, RAW, 32, 8>, c, c.K, 3, items, s, Dt, out, C2, D,
+                                             1);
+                    }
+                }
+            });
+        });
+    }
+};
 
 }  // namespace
 
 #define FHE_CAT2(a, b) a##b
 #define FHE_CAT(a, b) FHE_CAT2(a, b)
 const SplitOps *FHE_CAT(split_ops_, FHE_NTT_L)() {
-    static const SplitOps o = {split_tensor<FHE_NTT_L>, split_relin<FHE_NTT_L>};
+    typedef SplitL<FHE_NTT_L> S;
+    static const SplitOps o = {S::lift_fwd, S::fwd, S::blocks, S::inv, S::inv_scale, S::digits, S::relin};
     return &o;
 }

@@ -204,7 +204,9 @@ __device__ __forceinline__ void inv_pass_t(typename F::V (&x)[NR][16], int tid, 
     f.template pass_end<r, NR>(x);
 }
 
-template <bool LZ>
+// UNI: the prime is the same in the whole wave (its constants then live in
+// scalar registers).
+template <bool LZ, bool UNI = true>
 struct FieldU {
     typedef uint64_t V;
     typedef Tw T;
@@ -218,7 +220,12 @@ struct FieldU {
         q = P->q;
         qi = P->qinv_neg;
         one_p = P->one_p;
-        nq = neg_opaque(q);
+        if constexpr (UNI) {
+            nq = neg_opaque(q);
+        } else {
+            nq = 0 - q;
+            asm("" : "+v"(nq));
+        }
         tw = c.tw + (size_t)limb * c.n;
         itw = c.itw + (size_t)limb * c.n;
     }
@@ -398,14 +405,23 @@ struct FamU {
     static __device__ __forceinline__ void with(const DevCtx &c, int limb, const Fn &fn) {
         fn(FieldU<LZ>(c, limb));
     }
+    // the same with a prime per lane
+    template <class Fn>
+    static __device__ __forceinline__ void with_lanes(const DevCtx &c, int limb, const Fn &fn) {
+        fn(FieldU<LZ, false>(c, limb));
+    }
 };
 struct FamF {
     typedef double V;
     typedef TwF T;
     template <class Fn>
     static __device__ __forceinline__ void with(const DevCtx &c, int limb, const Fn &fn) {
-        if (c.pc[limb].q >= (1ull << 47)) fn(FieldF<true>(c, limb));
+        if ((c.big_limbs >> limb) & 1) fn(FieldF<true>(c, limb));
         else fn(FieldF<false>(c, limb));
+    }
+    template <class Fn>
+    static __device__ __forceinline__ void with_lanes(const DevCtx &c, int limb, const Fn &fn) {
+        with(c, limb, fn);
     }
 };
 
