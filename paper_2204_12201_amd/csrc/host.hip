@@ -203,6 +203,8 @@ struct EvPair {
 
 }  // namespace
 
+constexpr size_t kFusedAuto = SIZE_MAX - 1;
+
 struct fhe_ctx {
     int device = 0;
     uint32_t n = 0, L = 0, k = 0, kp = 0, K = 0, encoding = 0;
@@ -218,14 +220,14 @@ struct fhe_ctx {
     size_t batch_limit = 0, default_limit = 0;
     // fused product kernel (k_mul_tensor / k_square_tensor) from this many
     // (item, limb) workgroups per launch on; fewer take the unfused kernels
-    // (index 0: products of two ciphertexts, 1: squarings)
-    size_t fused_min_rows[2] = {128, 0};
+    // (index 0: products of two ciphertexts, 1: squarings).  kFusedAuto: the
+    // measured rule of fused_wanted
+    size_t fused_min_rows[2] = {kFusedAuto, kFusedAuto};
     // launches of the split transforms (kernels_split.hip), null for other ring
-    // degrees; key switching takes them below relin_split_rows (item, limb) rows
-    // where relin_split_ok says that its sums stay in range
+    // degrees; key switching takes them where relin_split_ok says that its sums
+    // stay in range and relin_is_split that they are faster
     const SplitOps *split = nullptr;
     bool relin_split_ok = false;
-    size_t relin_split_rows = 0;
     bool validate = false;
     bool timing = false;
     std::vector<EvPair> pending[KK_COUNT];
@@ -365,12 +367,36 @@ fhe_status check_canonical(fhe_ctx *c, const uint64_t *a, size_t nrows, int kmod
     return h ? FHE_ENONCANON : FHE_OK;
 }
 
-// The fused product kernel runs one workgroup per (item, limb) doing seven
-// transforms in a row; with few such workgroups the unfused kernels (one
-// workgroup per transform, seven times as many) finish sooner (measured at
-// n = 16384: one item faster unfused, sixteen faster fused): the default
-// threshold is 128 workgroups for products, and fhe_autotune_mul_relin moves
-// it (and the chunk size) per context from timings.
+// How full the last round of `rows` fused workgroups leaves the chip, which
+// holds 256 rows of n = 16384 at once (a workgroup of a smaller ring leaves room
+// for others on its CU): rows over the rows of whole rounds.
+double fused_fill(const fhe_ctx *c, size_t rows) {
+    const size_t round = (size_t)256 << (14 - c->L);
+    return (double)rows / (double)((rows + round - 1) / round * round);
+}
+
+// Whether the transform phase takes the fused kernel (one workgroup per row and
+// item) and not the split or, for rings without those, the unfused kernels.
+bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
+    const size_t rows = items * c->K, thr = c->fused_min_rows[square ? 1 : 0];
+    if (thr != kFusedAuto) return rows >= thr;
+    // rings without split transforms: measured at n = 16384, one product was
+    // faster unfused (seven times as many workgroups), sixteen fused
+    if (!c->split) return square || rows >= 128;
+    // floating-point fields have no fused kernels, and are faster at every size
+    // (n = 8192, 341 items: 1790 against 2562 us fused in integers; n = 4096,
+    // 512: 829 against 1011)
+    if (c->dev.f64) return false;
+    // without the matrix-core conversions the columns are not fused with them
+    if (!c->dev.mx) return rows >= (size_t)256 << (14 - c->L);
+    // products: the split kernels need four operand rows once where the fused
+    // one parks three (n = 16384, 16 items 470 against 481 us, 40: 1048 against
+    // 1182, 256: 5569 against 5772)
+    if (!square) return false;
+    // squares: the fused kernel is up to 2 % faster in whole rounds (32 items: 585
+    // against 593 us) and loses the rest of a partial one (24: 540 against 506)
+    return fused_fill(c, rows) >= 0.93;
+}
 
 // Transform phase of `items` products (squares when a == b): P rows of E from
 // the lift, tensor into Dt.  X: where the half-transformed rows may go (as
@@ -379,7 +405,7 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
                         size_t items, hipStream_t s) {
     const bool square = (a == b);
     const DevCtx &d = c->dev;
-    if (items * c->K >= c->fused_min_rows[square ? 1 : 0]) {
+    if (fused_wanted(c, square, items)) {
         if (square)
             return run(c, KK_SQUARE_TENSOR, s, [&] { return launch_square_tensor(d, a, E, Dt, items, s); });
         return run(c, KK_MUL_TENSOR, s, [&] { return launch_mul_tensor(d, a, b, E, Dt, items, s); });
@@ -393,9 +419,12 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
     return run(c, KK_TENSOR_INTT, s, [&] { return launch_tensor_intt(d, E, Dt, square, items, s); });
 }
 
-// Whether key switching of `items` ciphertexts takes the split kernels.
+// Whether key switching of `items` ciphertexts takes the split kernels: always
+// in doubles; in integers they cost about 5 % more than whole rounds of the fused
+// kernel (n = 16384, 128 items: 2916 against 2797 us) and win where it leaves
+// the chip part empty (33 items, two rounds: 865 against 984; 56: equal).
 bool relin_is_split(const fhe_ctx *c, size_t items) {
-    return c->relin_split_ok && items * c->k < c->relin_split_rows;
+    return c->relin_split_ok && (c->dev.f64 || fused_fill(c, items * c->k) < 0.85);
 }
 
 // Key switching of C2 [items][k][n] added to out.  scratch: `words` words that
@@ -447,7 +476,7 @@ fhe_status mul_relin_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, co
         uint64_t *Dt = E + items * npoly * K * n;
         uint64_t *C2 = Dt + items * 3 * K * n;
         const DevCtx &d = c->dev;
-        if (c->split && d.mx && items * K < c->fused_min_rows[square ? 1 : 0]) {
+        if (c->split && d.mx && !fused_wanted(c, square, items)) {
             FHE_TRY(split_products(c, rlk, ai, bi, oi, E, Dt, C2, items, relin, s));
             continue;
         }
@@ -771,6 +800,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
         P.r32 = (uint64_t)(((u128)1 << 32) % q);
         P.r32_p = shoup(P.r32, q);
         P.mx_neg_bias = (q - (uint64_t)(((u128)FHE_MX_BIAS * 0x0101010101010101ull) % q)) % q;
+        P.c96 = q > (1ull << 33) ? (uint64_t)(((u128)1 << 96) / q) : 0;
         P.off59 = ((1ull << 59) + q - 1) / q * q;
         P.off62 = ((1ull << 62) + q - 1) / q * q;
         const double qinv = 1.0 / (double)q;
@@ -974,18 +1004,6 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     // 4 (L + 1) q by column products, whose high halves must not overflow
     c->split = split_ops((int)c->L);
     c->relin_split_ok = c->split && (f64 || (d.lazy_q && qmax < (1ull << 58)));
-    if (c->split) {
-        // Integer fields: the fused kernels need a workgroup per row on every CU
-        // (256 rows of 16384, which fill a CU each); below that the split ones
-        // spread over the chip (n = 16384, products: 1 item 107 against 323 us,
-        // 8 items 284 against 344; 16 items 495 against 497; 32 items 862
-        // against 768).  Floating-point fields have no fused kernels and beat
-        // the integer ones at every size (n = 8192, 341 items: 2086 against
-        // 2562 us; n = 4096, 512 items: 931 against 1011).
-        const size_t full = f64 ? SIZE_MAX : (size_t)256 << (14 - c->L);
-        c->fused_min_rows[0] = c->fused_min_rows[1] = full;
-        c->relin_split_rows = full;
-    }
     // default chunk: about 8 GiB of product workspace
     size_t per = item_words_mul(c, false) * 8;
     c->default_limit = ((size_t)8 << 30) / per;

@@ -17,6 +17,7 @@
 // outputs and stay in the L2 / last-level cache between blocks.
 #include "kernels.hpp"
 #include "modarith.hpp"
+#include "ntt_core.hpp"
 
 namespace {
 
@@ -129,7 +130,12 @@ __global__ __launch_bounds__(256) void k_weighted_sum(DevCtx c, const uint64_t *
 // x = P'_0 + 2^8 P'_1 + 2^16 P'_2 + 2^24 P'_3 and w = P'_4 + ... + 2^24 P'_7
 // (both below 2^47), A = floor(x / 2^32) + w and B = x mod 2^32.  With E =
 // -FHE_MX_BIAS sum_u 256^u mod q (PrimeConst::mx_neg_bias) added, T' + E is
-// the sum modulo q: (A + E_hi) r32 + (B + E_lo), two Shoup products.
+// the sum modulo q, hi 2^32 + lo with hi < 2^48 and lo < 2^33.  For q > 2^33 one
+// quotient serves: h = floor(hi floor(2^96 / q) / 2^64), taken from three of the
+// four partial products, is at most 4 below hi 2^32 / q, so hi 2^32 + lo - h q
+// (exact modulo 2^64) lies in [0, 5q) plus lo < q.  Smaller primes take
+// hi r32 + lo, two Shoup products.  The kernel was bound by this arithmetic, not
+// by its stores: 24 inputs, 300 outputs at n = 16384, see wsx_reduce.
 //
 // Operand layout (as for the base conversions): lane l of a wave supplies row
 // l mod 16 of A (output 16 mt + l mod 16) and column l mod 16 of B (word
@@ -155,6 +161,18 @@ __device__ __forceinline__ uint32_t ws_gather(const uint64_t *d, int u) {
     return r;
 }
 
+// hi 2^32 + lo mod q, canonical (bounds above).  c96 is the same in the wave.
+__device__ __forceinline__ uint64_t wsx_reduce(uint64_t hi, uint64_t lo, uint64_t q, uint64_t nq, uint64_t c96,
+                                               uint64_t r32, uint64_t r32p, uint64_t onep) {
+    if (c96) {
+        const uint32_t a0 = (uint32_t)hi, a1 = (uint32_t)(hi >> 32), b0 = (uint32_t)c96, b1 = (uint32_t)(c96 >> 32);
+        uint64_t h = (uint64_t)a1 * b1 + mulhi32(a1, b0);
+        h += mulhi32(a0, b1);
+        return canon8w(h * nq + ((hi << 32) + lo), q);
+    }
+    return canon8w(mul_shoup_lazy4(hi, r32, r32p, q) + mul_shoup_lazy4(lo, 1, onep, q), q);
+}
+
 // Wave w of workgroup x takes word positions p0 = 16 (WSX_WAVES x + w) .. p0 + 15
 // (input j at in + j in_js, output m at out + m out_ms) for the output tiles
 // blockIdx.y, blockIdx.y + gridDim.y, ... < nmt; wt: the pass's A operands
@@ -172,7 +190,8 @@ __global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, co
     // the prime's constants in registers (a store to out could alias the
     // table for the compiler, which would reload them, and wait, per output)
     const PrimeConst &P = c.pc[limb];
-    const uint64_t q = P.q, E = P.mx_neg_bias, r32 = P.r32, r32p = P.r32_p, onep = P.one_p;
+    const uint64_t q = P.q, E = P.mx_neg_bias, r32 = P.r32, r32p = P.r32_p, onep = P.one_p,
+                   c96 = P.c96, nq = neg_opaque(q);
     // digits of the lane's 16 inputs, then one B operand per digit u
     uint64_t d[16];
 #pragma unroll
@@ -202,7 +221,7 @@ __global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, co
             const uint64_t x = (uint64_t)a01 + ((uint64_t)a23 << 16);
             const uint64_t w = (uint64_t)a45 + ((uint64_t)a67 << 16);
             const uint64_t hi = (x >> 32) + w + (E >> 32), lo = (x & 0xFFFFFFFFull) + (uint32_t)E;
-            uint64_t r = canon8w(mul_shoup_lazy4(hi, r32, r32p, q) + mul_shoup_lazy4(lo, 1, onep, q), q);
+            uint64_t r = wsx_reduce(hi, lo, q, nq, c96, r32, r32p, onep);
             uint64_t *o = out + m * out_ms + p;
             if (accumulate) r = add_mod(r, *o, q);
             *o = r;

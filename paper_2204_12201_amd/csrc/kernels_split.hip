@@ -659,7 +659,7 @@ struct SplitL {
     static hipError_t tensor_field(const DevCtx &c, const Fn &fn) {
         if (c.f64) fn(FamF());
         else if (c.lazy_all) fn(FamU<true>());
-        else fn(FamU<false>());
+        else fn(FamM());
         return hipGetLastError();
     }
     // fn(field family of key switching, digits enter as they are)

@@ -411,6 +411,22 @@ struct FamU {
         fn(FieldU<LZ, false>(c, limb));
     }
 };
+// Integer primes of both kinds: the lazy butterflies where the prime allows
+// them (the primes of Q do where P needs primes too large).
+struct FamM {
+    typedef uint64_t V;
+    typedef Tw T;
+    template <class Fn>
+    static __device__ __forceinline__ void with(const DevCtx &c, int limb, const Fn &fn) {
+        if ((c.lazy_limbs >> limb) & 1) fn(FieldU<true>(c, limb));
+        else fn(FieldU<false>(c, limb));
+    }
+    template <class Fn>
+    static __device__ __forceinline__ void with_lanes(const DevCtx &c, int limb, const Fn &fn) {
+        if ((c.lazy_limbs >> limb) & 1) fn(FieldU<true, false>(c, limb));
+        else fn(FieldU<false, false>(c, limb));
+    }
+};
 struct FamF {
     typedef double V;
     typedef TwF T;
