@@ -370,7 +370,8 @@ fhe_status fhe_gate(fhe_ctx *ctx, const uint64_t *rlk_dev, int gate, const uint6
  * e_i = 1 - ((a_i + b_i) - p_i - p_i) (XNOR); lt = d_0, then for i >= 1
  * lt = e_i (lt - d_i) + d_i (MUX(e_i, lt, d_i)).  Multiplicative depth nbits.
  *   a, b device [count][nbits][2][k][n];  out device [count][2][k][n]
- * nbits >= 1.  ws: FHE_OP_COMPARE bytes for count. */
+ * nbits >= 1.  ws: FHE_OP_COMPARE bytes for count; with 6 ciphertexts per item
+ * plus FHE_OP_MUL_RELIN bytes the bits go one after the other (same words). */
 fhe_status fhe_less_than(fhe_ctx *ctx, const uint64_t *rlk_dev, const uint64_t *a, const uint64_t *b,
                          uint32_t nbits, uint64_t *out, size_t count, void *ws, size_t ws_bytes,
                          hipStream_t stream);
@@ -380,7 +381,9 @@ fhe_status fhe_less_than(fhe_ctx *ctx, const uint64_t *rlk_dev, const uint64_t *
  * (fhe_less_than); out_a takes the factor 1 - l, out_b the factor l; a class's
  * first factor is copied, later ones multiplied in (fhe_mul_relin).
  *   scores device [ncls][count][nbits][2][k][n];  out device [ncls][count][2][k][n]
- * 2 <= ncls <= 16.  ws: FHE_OP_ARGMAX bytes for count. */
+ * 2 <= ncls <= 16.  ws: FHE_OP_ARGMAX bytes for count; with 8 ciphertexts per
+ * item plus FHE_OP_MUL_RELIN bytes the comparisons go one after the other (same
+ * words). */
 fhe_status fhe_argmax(fhe_ctx *ctx, const uint64_t *rlk_dev, const uint64_t *scores, uint32_t ncls,
                       uint32_t nbits, uint64_t *out, size_t count, void *ws, size_t ws_bytes,
                       hipStream_t stream);

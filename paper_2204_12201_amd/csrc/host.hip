@@ -495,23 +495,50 @@ uint64_t *c2_of_single_chunk(const fhe_ctx *c, void *ws, size_t count, bool squa
     return (uint64_t *)ws + count * npoly * K * n + count * 3 * K * n;
 }
 
-// Products of `count` items from transformed operands (k_lift + k_fwd_ext
-// layout [.][2][K][n]): item z multiplies input z mod na of Ahat by entry z of
-// Bhat; chunks of the batch cap, workspace as for products.
+// Transforms of both polynomials of `items` ciphertexts at a, the operands of
+// mul_relin_pre2_impl, into That [items][2][K][n]: canonical, or with `split`
+// (the same for every operand of a product) field values of the split transforms.
+fhe_status transform_operands(fhe_ctx *c, const uint64_t *a, uint64_t *That, size_t items, bool split, hipStream_t s) {
+    const DevCtx &d = c->dev;
+    if (split) {
+        FHE_TRY(run(c, KK_LIFT, s, [&] { return c->split->lift_fwd(d, a, a, That, 2, items, s); }));
+        return run(c, KK_FWD_EXT, s, [&] { return c->split->fwd_blocks(d, That, items, s); });
+    }
+    FHE_TRY(run(c, KK_LIFT, s, [&] { return launch_lift(d, a, a, That, 2, items, s); }));
+    return run(c, KK_FWD_EXT, s, [&] { return launch_fwd_ext(d, a, a, That, 2, items, s); });
+}
+
+// Products of `count` items from transformed operands [.][2][K][n]
+// (transform_operands): item z multiplies input z mod na of Ahat by entry z of
+// Bhat; chunks of the batch cap, workspace as for products of two ciphertexts.
 fhe_status mul_relin_pre2_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t *Ahat, size_t na,
-                               const uint64_t *Bhat, uint64_t *out, size_t count, void *ws, hipStream_t s) {
-    const size_t n = c->n, K = c->K, ctw = ct_words(c);
+                               const uint64_t *Bhat, uint64_t *out, size_t count, void *ws, bool split,
+                               hipStream_t s) {
+    const size_t n = c->n, K = c->K, k = c->k, ctw = ct_words(c);
     const size_t chunk = c->batch_limit;
     const DevCtx &d = c->dev;
     for (size_t off = 0; off < count; off += chunk) {
         const size_t items = count - off < chunk ? count - off : chunk;
         uint64_t *oi = out + off * ctw;
-        uint64_t *Dt = (uint64_t *)ws;
-        uint64_t *C2 = Dt + items * 3 * K * n;
-        FHE_TRY(run(c, KK_MUL_TENSOR, s,
-                    [&] { return launch_mul_tensor_pre2(d, Ahat, (int)na, off, Bhat, Dt, items, s); }));
-        FHE_TRY(run(c, KK_SCALE, s, [&] { return launch_scale(d, Dt, oi, C2, items, s); }));
-        FHE_TRY(relin_phase(c, C2, rlk, oi, items, Dt, items * 3 * K * n, s));
+        // C2, the tensor, and what is left of the 7K + k rows per item
+        uint64_t *C2 = (uint64_t *)ws;
+        uint64_t *Dt = C2 + items * k * n, *rest = Dt + items * 3 * K * n;
+        if (split) {
+            FHE_TRY(run(c, KK_SPLIT_TENSOR, s,
+                        [&] { return c->split->pre2(d, Ahat, na, off, Bhat, Dt, items, s); }));
+            const bool direct = relin_is_split(c, items) && k * k <= 4 * K;
+            FHE_TRY(run(c, KK_SCALE, s,
+                        [&] { return c->split->inv_scale(d, Dt, oi, C2, direct ? rest : nullptr, items, s); }));
+            if (direct) {
+                FHE_TRY(run(c, KK_SPLIT_RELIN, s, [&] { return c->split->relin(d, rest, rlk, Dt, oi, items, s); }));
+                continue;
+            }
+        } else {
+            FHE_TRY(run(c, KK_MUL_TENSOR, s,
+                        [&] { return launch_mul_tensor_pre2(d, Ahat, (int)na, off, Bhat, Dt, items, s); }));
+            FHE_TRY(run(c, KK_SCALE, s, [&] { return launch_scale(d, Dt, oi, C2, items, s); }));
+        }
+        FHE_TRY(relin_phase(c, C2, rlk, oi, items, Dt, items * 7 * K * n, s));
     }
     return FHE_OK;
 }
@@ -1026,6 +1053,32 @@ size_t fhe_pk_words(const fhe_ctx *c) { return c ? ct_words(c) : 0; }
 size_t fhe_rlk_words(const fhe_ctx *c) { return c ? 2 * (size_t)c->k * c->k * c->n : 0; }
 uint32_t fhe_aux_primes(const fhe_ctx *c) { return c ? c->kp : 0; }
 
+// Workspace of a comparison one bit after the other.
+static size_t compare_seq_bytes(const fhe_ctx *c, size_t count) {
+    return 6 * count * ct_words(c) * 8 + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, count);
+}
+
+// Workspace of an argmax one comparison after the other.
+static size_t argmax_seq_bytes(const fhe_ctx *c, size_t count) {
+    return 2 * count * ct_words(c) * 8 + compare_seq_bytes(c, count);
+}
+
+// Workspace of a group of `pairs` comparisons with all bit products in one
+// batch (lt_group): gathered operands (two or more pairs), products, e and t.
+static size_t lt_group_bytes(const fhe_ctx *c, size_t pairs, size_t count, size_t nbits) {
+    const size_t items = pairs * count * nbits;
+    return ((pairs > 1 ? 3 : 1) * items + 2 * pairs * count) * ct_words(c) * 8 +
+           fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, items);
+}
+
+// Bits per item that the workspace sizes make room for: batches of up to 64
+// products of n = 16384 (about four times what the chip's CUs hold of one
+// product's blocks), at least the 2 and at most the 8 of a comparison.
+static size_t lt_bits_room(const fhe_ctx *c, size_t rows) {
+    const size_t batch = ((size_t)64 << 14) / c->n, most = rows ? (batch + rows - 1) / rows : 2;
+    return most < 2 ? 2 : most > 8 ? 8 : most;
+}
+
 size_t fhe_workspace_bytes(const fhe_ctx *c, int op, size_t count) {
     if (!c) return 0;
     const size_t n = c->n, k = c->k;
@@ -1058,10 +1111,19 @@ size_t fhe_workspace_bytes(const fhe_ctx *c, int op, size_t count) {
             return 81 * count + 1024;
         case FHE_OP_GATE:
             return 2 * count * ct_words(c) * 8 + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, count);
-        case FHE_OP_COMPARE:
-            return 6 * count * ct_words(c) * 8 + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, count);
-        case FHE_OP_ARGMAX:
-            return 2 * count * ct_words(c) * 8 + fhe_workspace_bytes(c, FHE_OP_COMPARE, count);
+        case FHE_OP_COMPARE: {
+            // one bit at a time, or room for the bits of a comparison side by side
+            // (lt_group_bytes; the call takes what fits)
+            const size_t a = compare_seq_bytes(c, count), b = lt_group_bytes(c, 1, count, lt_bits_room(c, count));
+            return a > b ? a : b;
+        }
+        case FHE_OP_ARGMAX: {
+            // one comparison at a time, or room for the bits of three pairs side
+            // by side, with the results of six pairs and a factor per class
+            const size_t a = argmax_seq_bytes(c, count);
+            const size_t b = 10 * count * ct_words(c) * 8 + lt_group_bytes(c, 3, count, lt_bits_room(c, 3 * count));
+            return a > b ? a : b;
+        }
         case FHE_OP_BRIDGE_POWERS: {
             if (c->t < 3 || c->t > 257) return 0;
             const size_t e = c->t - 1;
@@ -1926,6 +1988,39 @@ static fhe_status less_than_impl(fhe_ctx *c, const uint64_t *rlk, const uint64_t
     return FHE_OK;
 }
 
+// Comparisons of `pairs` (at most kLtPairs) pairs of bit vectors with the bit
+// products of all of them in one batch: the products a_i b_i do not depend on
+// one another, so only the nbits - 1 selections follow one another, each batched
+// over the pairs.  The same products and sums as less_than_impl, word for word.
+// lt [pairs][count]; ws: lt_group_bytes.
+static fhe_status lt_group(fhe_ctx *c, const uint64_t *rlk, const LtPairs &P, size_t pairs, uint32_t nbits,
+                           uint64_t *lt, size_t count, void *ws, hipStream_t st) {
+    const size_t ctw = ct_words(c), vec = count * nbits * ctw, rows = pairs * count;
+    uint64_t *Pr = (uint64_t *)ws, *E = Pr + pairs * vec, *T = E + rows * ctw, *G = T + rows * ctw;
+    void *mws = pairs > 1 ? G + 2 * pairs * vec : G;
+    const uint64_t *A = P.a[0], *B = P.b[0];
+    if (pairs > 1) {
+        for (size_t q = 0; q < pairs; q++) {
+            FHE_HIP(hipMemcpyAsync(G + q * vec, P.a[q], vec * 8, hipMemcpyDeviceToDevice, st));
+            FHE_HIP(hipMemcpyAsync(G + (pairs + q) * vec, P.b[q], vec * 8, hipMemcpyDeviceToDevice, st));
+        }
+        A = G;
+        B = G + pairs * vec;
+    }
+    FHE_TRY(mul_relin_impl(c, rlk, A, B, Pr, rows * nbits, mws, st));
+    for (uint32_t i = 1; i <= nbits; i++) {
+        FHE_TRY(run(c, KK_ELEMENTWISE, st, [&] {
+            return launch_lt_step(c->dev, P, (int)pairs, (int)count, (int)nbits, (int)i, Pr, E, T, lt, st);
+        }));
+        if (i < nbits) FHE_TRY(mul_relin_impl(c, rlk, E, T, T, rows, mws, st));
+    }
+    return FHE_OK;
+}
+
+// Whether one more than `count` items' products still share the chip: beyond
+// about 64 products of n = 16384 a batch gains nothing from being larger.
+static bool lt_small(const fhe_ctx *c, size_t items) { return items * c->n <= ((size_t)128 << 14); }
+
 fhe_status fhe_less_than(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, const uint64_t *b, uint32_t nbits,
                          uint64_t *out, size_t count, void *ws, size_t ws_bytes, hipStream_t st) {
     if (!c) return FHE_EINVAL;
@@ -1935,9 +2030,16 @@ fhe_status fhe_less_than(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, con
     const size_t ctb = ct_words(c) * 8;
     if (overlaps2(out, count * ctb, a, count * nbits * ctb) || overlaps2(out, count * ctb, b, count * nbits * ctb))
         return FHE_EINVAL;
-    if (ws_bytes < fhe_workspace_bytes(c, FHE_OP_COMPARE, count)) return FHE_EWORKSPACE;
+    if (ws_bytes < compare_seq_bytes(c, count)) return FHE_EWORKSPACE;  // enough for one bit at a time
     FHE_TRY(check_canonical(c, a, count * nbits * 2 * c->k, c->k, 0, st));
     FHE_TRY(check_canonical(c, b, count * nbits * 2 * c->k, c->k, 0, st));
+    // a == b squares every bit; the general path keeps its single buffers
+    if (a != b && nbits > 1 && lt_small(c, count * nbits) && ws_bytes >= lt_group_bytes(c, 1, count, nbits)) {
+        LtPairs P{};
+        P.a[0] = a;
+        P.b[0] = b;
+        return lt_group(c, rlk, P, 1, nbits, out, count, ws, st);
+    }
     return less_than_impl(c, rlk, a, b, nbits, out, count, ws, st);
 }
 
@@ -1949,8 +2051,42 @@ fhe_status fhe_argmax(fhe_ctx *c, const uint64_t *rlk, const uint64_t *scores, u
     if (!rlk || !scores || !out || !ws) return FHE_EINVAL;
     const size_t ctw = ct_words(c), cw = count * ctw, sw = count * nbits * ctw;
     if (overlaps2(out, ncls * cw * 8, scores, ncls * sw * 8)) return FHE_EINVAL;
-    if (ws_bytes < fhe_workspace_bytes(c, FHE_OP_ARGMAX, count)) return FHE_EWORKSPACE;
+    if (ws_bytes < argmax_seq_bytes(c, count)) return FHE_EWORKSPACE;  // enough for one comparison at a time
     FHE_TRY(check_canonical(c, scores, ncls * count * nbits * 2 * c->k, c->k, 0, st));
+    // Groups of pairs side by side where the batches stay small enough to gain
+    // and the workspace holds them (fhe_workspace_bytes makes room for three pairs)
+    const size_t np = (size_t)ncls * (ncls - 1) / 2;
+    if (nbits > 1 && lt_small(c, count * nbits)) {
+        const size_t fixed = (np + ncls) * cw * 8;
+        size_t per = np < (size_t)kLtPairs ? np : kLtPairs;
+        while (per > 0 && (fixed + lt_group_bytes(c, per, count, nbits) > ws_bytes ||
+                           (per > 1 && !lt_small(c, per * count * nbits))))
+            per--;
+        // the factors' products share the groups' product workspace
+        if (per > 0 && fixed + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, ncls * count) <= ws_bytes) {
+            uint64_t *lt = (uint64_t *)ws, *Y = lt + np * cw;
+            void *gws = Y + ncls * cw;
+            LtPairs P{};
+            size_t have = 0, done = 0;
+            for (uint32_t a = 0; a < ncls; a++)
+                for (uint32_t b = a + 1; b < ncls; b++) {
+                    P.a[have] = scores + a * sw;
+                    P.b[have++] = scores + b * sw;
+                    if (have == per || done + have == np) {
+                        FHE_TRY(lt_group(c, rlk, P, have, nbits, lt + done * cw, count, gws, st));
+                        done += have;
+                        have = 0;
+                    }
+                }
+            for (uint32_t t = 1; t < ncls; t++) {
+                uint64_t *dst = t == 1 ? out : Y;
+                FHE_TRY(run(c, KK_ELEMENTWISE, st,
+                            [&] { return launch_argmax_factor(c->dev, lt, (int)ncls, (int)count, (int)t, dst, st); }));
+                if (t > 1) FHE_TRY(mul_relin_impl(c, rlk, out, Y, out, ncls * count, gws, st));
+            }
+            return FHE_OK;
+        }
+    }
     uint64_t *Lt = (uint64_t *)ws, *Na = Lt + cw;
     void *cws = Na + cw;
     void *mws = (uint8_t *)cws + 6 * cw * 8;  // the comparison's product workspace
@@ -2022,27 +2158,21 @@ fhe_status fhe_bridge_to_bits_powers(fhe_ctx *c, const uint64_t *rlk, const uint
     std::vector<int32_t> W;
     bridge_weights(c->t, nbits, W);
     FHE_TRY(stage_weights(c, W.data(), nbits, c->t, wd, st));
-    const DevCtx &d = c->dev;
+    const bool split = c->split && c->dev.mx;
     for (size_t g0 = 0; g0 < count; g0 += G) {
         const size_t gc = count - g0 < G ? count - g0 : G;
         const size_t bw = gc * ctw;      // one power of every input of the group
         const size_t tb = gc * tw_words; // its transform
         FHE_HIP(hipMemcpyAsync(Pw, x + g0 * ctw, bw * 8, hipMemcpyDeviceToDevice, st));
-        FHE_TRY(run(c, KK_LIFT, st, [&] { return launch_lift(d, Pw, Pw, T, 2, gc, st); }));
-        FHE_TRY(run(c, KK_FWD_EXT, st, [&] { return launch_fwd_ext(d, Pw, Pw, T, 2, gc, st); }));
+        FHE_TRY(transform_operands(c, Pw, T, gc, split, st));
         // level of x^(h+1) .. x^(2h): x^(h+r) = x^h x^r, r = 1..min(h, e - h),
         // from the cached transforms; the new powers up to hmax are then
         // lifted and transformed once for the later levels
         for (size_t h = 1; h < e; h *= 2) {
             const size_t nk = (2 * h <= e ? 2 * h : e) - h;
-            FHE_TRY(mul_relin_pre2_impl(c, rlk, T + (h - 1) * tb, gc, T, Pw + h * bw, nk * gc, mws, st));
+            FHE_TRY(mul_relin_pre2_impl(c, rlk, T + (h - 1) * tb, gc, T, Pw + h * bw, nk * gc, mws, split, st));
             const size_t keep = h + nk <= hmax ? nk : (h < hmax ? hmax - h : 0);
-            if (keep) {
-                const uint64_t *np = Pw + h * bw;
-                uint64_t *nt = T + h * tb;
-                FHE_TRY(run(c, KK_LIFT, st, [&] { return launch_lift(d, np, np, nt, 2, keep * gc, st); }));
-                FHE_TRY(run(c, KK_FWD_EXT, st, [&] { return launch_fwd_ext(d, np, np, nt, 2, keep * gc, st); }));
-            }
+            if (keep) FHE_TRY(transform_operands(c, Pw + h * bw, T + h * tb, keep * gc, split, st));
         }
         FHE_TRY(run(c, KK_ELEMENTWISE, st, [&] {
             return launch_weighted_sum_items(c->dev, Pw, bw, ctw, c->t, 1, wd, nbits, bits + g0 * nbits * ctw, ctw,

@@ -69,6 +69,12 @@ struct SplitOps {
                       size_t items, hipStream_t s);
     // Dt [items][3][K][n]: tensor of X
     hipError_t (*blocks)(const DevCtx &, const uint64_t *X, uint64_t *Dt, bool square, size_t items, hipStream_t s);
+    // X [items][2][K][n]: the rest of the forward transforms, in place
+    hipError_t (*fwd_blocks)(const DevCtx &, uint64_t *X, size_t items, hipStream_t s);
+    // Dt: tensor of transformed operands, item z of input (item0 + z) mod na of
+    // Ahat and entry item0 + z of Bhat ([.][2][K][n])
+    hipError_t (*pre2)(const DevCtx &, const uint64_t *Ahat, size_t na, size_t item0, const uint64_t *Bhat,
+                       uint64_t *Dt, size_t items, hipStream_t s);
     // Dt finished in place, canonical
     hipError_t (*inv)(const DevCtx &, uint64_t *Dt, size_t items, hipStream_t s);
     // Dt finished, scaled and rounded: components 0, 1 to out; component 2 to D
@@ -179,6 +185,15 @@ hipError_t launch_bridge_combine(const DevCtx &c, const uint64_t *y, uint64_t *b
 // out = sum_b 2^b bits[b] by Horner; signed_top: the leading bit weighs -2^(nbits-1)
 hipError_t launch_horner(const DevCtx &c, const uint64_t *bits, int nbits, uint64_t *out,
                          size_t count, int signed_top, hipStream_t s);
+// Comparisons of up to kLtPairs pairs of bit vectors (k_lt_step, k_argmax_factor).
+constexpr int kLtPairs = 16;
+struct LtPairs {
+    const uint64_t *a[kLtPairs], *b[kLtPairs];
+};
+hipError_t launch_lt_step(const DevCtx &c, const LtPairs &P, int pairs, int count, int nbits, int i,
+                          const uint64_t *Pr, uint64_t *E, uint64_t *T, uint64_t *lt, hipStream_t s);
+hipError_t launch_argmax_factor(const DevCtx &c, const uint64_t *lt, int ncls, int count, int t, uint64_t *out,
+                                hipStream_t s);
 // flag[0] |= 1 if some word of rows [nrows][n] (limb = row % kmod + off) is >= its prime
 hipError_t launch_validate(const DevCtx &c, const uint64_t *a, size_t nrows, int kmod, int off,
                            unsigned int *flag, hipStream_t s);

@@ -476,6 +476,60 @@ __global__ void k_horner(DevCtx c, const uint64_t *__restrict__ bits, int nbits,
     }
 }
 
+// One step of the comparisons of a group of pairs (fhe_less_than's circuit,
+// bits i = 0 .. nbits of every pair's items at once): row blockIdx.y = q count +
+// j is item j of pair q, whose bit vectors are P.a[q], P.b[q] [count][nbits]; Pr
+// [pairs][count][nbits] holds the products a_i b_i and T the last product
+// e (lt - d).  With d_i = b_i - a_i b_i and lt = d_0 or T + d_(i-1):
+// i < nbits: E = e_i = 1 - ((a_i + b_i) - 2 a_i b_i), T = lt - d_i;
+// i == nbits: the result to lt.  grid (2 k n / 256, pairs count).  Bound by its
+// seven streams; the steps it replaces were seven launches a bit.
+__global__ __launch_bounds__(256) void k_lt_step(DevCtx c, LtPairs P, int count, int nbits, int i,
+                                                 const uint64_t *__restrict__ Pr, uint64_t *__restrict__ E,
+                                                 uint64_t *__restrict__ T, uint64_t *__restrict__ lt) {
+    const uint32_t W = 2u * c.k * c.n, p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= W) return;
+    const int limb = (int)((p >> c.L) % (uint32_t)c.k);
+    const uint64_t q = c.pc[limb].q;
+    const int y = (int)blockIdx.y, pair = y / count, j = y % count;
+    const uint64_t *a = P.a[pair] + (size_t)j * nbits * W + p, *b = P.b[pair] + (size_t)j * nbits * W + p;
+    const uint64_t *pr = Pr + (size_t)y * nbits * W + p;
+    const size_t o = (size_t)y * W + p;
+    uint64_t l = 0;
+    if (i > 0) {
+        l = sub_mod(b[(size_t)(i - 1) * W], pr[(size_t)(i - 1) * W], q);
+        if (i > 1) l = add_mod(T[o], l, q);
+    }
+    if (i == nbits) {
+        lt[o] = l;
+        return;
+    }
+    const uint64_t av = a[(size_t)i * W], bv = b[(size_t)i * W], pv = pr[(size_t)i * W];
+    const uint64_t one = p < (uint32_t)(c.k * c.n) && (p & (c.n - 1)) == 0 ? c.cc->delta_q[limb] : 0;
+    const uint64_t s = sub_mod(sub_mod(add_mod(av, bv, q), pv, q), pv, q);
+    E[o] = sub_mod(one, s, q);
+    T[o] = sub_mod(l, sub_mod(bv, pv, q), q);
+}
+
+// Factor t (1 .. ncls - 1) of every class of the one-hot argmax: class cl meets
+// the others in ascending order; against o < cl the factor is lt of the pair
+// (o, cl), against o > cl it is 1 - lt of (cl, o).  lt [pairs][count], pairs
+// ordered by first class, then second; out [ncls][count].  grid (2 k n / 256,
+// ncls count).
+__global__ __launch_bounds__(256) void k_argmax_factor(DevCtx c, const uint64_t *__restrict__ lt, int ncls, int count,
+                                                       int t, uint64_t *__restrict__ out) {
+    const uint32_t W = 2u * c.k * c.n, p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= W) return;
+    const int limb = (int)((p >> c.L) % (uint32_t)c.k);
+    const uint64_t q = c.pc[limb].q;
+    const int y = (int)blockIdx.y, cl = y / count, j = y % count, o = t <= cl ? t - 1 : t;
+    const int lo = o < cl ? o : cl, hi = o < cl ? cl : o;
+    const size_t pair = (size_t)lo * (2 * ncls - lo - 1) / 2 + (hi - lo - 1);
+    const uint64_t v = lt[(pair * count + j) * W + p];
+    const uint64_t one = p < (uint32_t)(c.k * c.n) && (p & (c.n - 1)) == 0 ? c.cc->delta_q[limb] : 0;
+    out[(size_t)y * W + p] = o < cl ? v : sub_mod(one, v, q);
+}
+
 __global__ void k_validate(DevCtx c, const uint64_t *__restrict__ a, size_t words, int kmod, int off,
                            unsigned int *flag) {
     const size_t n = c.n;
@@ -929,6 +983,22 @@ hipError_t launch_horner(const DevCtx &c, const uint64_t *bits, int nbits, uint6
     const size_t words = count * 2 * c.k * (size_t)c.n;
     if (words == 0) return hipSuccess;
     hipLaunchKernelGGL(k_horner, dim3(grid_for(words)), dim3(256), 0, s, c, bits, nbits, out, count, signed_top);
+    return hipGetLastError();
+}
+
+hipError_t launch_lt_step(const DevCtx &c, const LtPairs &P, int pairs, int count, int nbits, int i,
+                          const uint64_t *Pr, uint64_t *E, uint64_t *T, uint64_t *lt, hipStream_t s) {
+    const unsigned W = 2u * (unsigned)c.k * (unsigned)c.n;
+    hipLaunchKernelGGL(k_lt_step, dim3((W + 255) / 256, (unsigned)(pairs * count)), dim3(256), 0, s, c, P, count, nbits,
+                       i, Pr, E, T, lt);
+    return hipGetLastError();
+}
+
+hipError_t launch_argmax_factor(const DevCtx &c, const uint64_t *lt, int ncls, int count, int t, uint64_t *out,
+                                hipStream_t s) {
+    const unsigned W = 2u * (unsigned)c.k * (unsigned)c.n;
+    hipLaunchKernelGGL(k_argmax_factor, dim3((W + 255) / 256, (unsigned)(ncls * count)), dim3(256), 0, s, c, lt, ncls,
+                       count, t, out);
     return hipGetLastError();
 }
 

@@ -205,8 +205,13 @@ __global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, co
         Bu[u] = ws_v4i{(int)ws_gather(d, u), (int)ws_gather(d + 4, u), (int)ws_gather(d + 8, u),
                        (int)ws_gather(d + 12, u)};
     const ws_v4i bias = {FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS};
+    // the next tile's weights are fetched before this tile's stores: vector
+    // memory completes in order, so a load behind them would wait for them
+    ws_v4i An = wt[(size_t)blockIdx.y * 64 + lane];
     for (int mt = (int)blockIdx.y; mt < nmt; mt += (int)gridDim.y) {
-        const ws_v4i A = wt[(size_t)mt * 64 + lane];
+        const ws_v4i A = An;
+        const int next = mt + (int)gridDim.y;
+        An = wt[(size_t)(next < nmt ? next : mt) * 64 + lane];
         ws_v4i acc[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bu[u], bias, 0, 0, 0);

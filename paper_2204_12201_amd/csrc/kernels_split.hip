@@ -414,6 +414,86 @@ __global__ __launch_bounds__(64 * W) void k_split_tensor_many(DevCtx c, const ui
     });
 }
 
+// Operands kept transformed (the powers of the bridge): k_split_ops finishes
+// the forward transforms in place, operands' values ready for products;
+// k_split_pre2 multiplies two of them and runs the inverse's block part.  Grids
+// (K n/1024, item groups) of W waves as for k_split_tensor_many.
+template <int L, class F, int W>
+__global__ __launch_bounds__(64 * W) void k_split_ops(DevCtx c, uint64_t *__restrict__ X, size_t items) {
+    typedef typename F::V V;
+    typedef TwBlock<typename F::T> TW;
+    constexpr int n = Geo<L>::N, NB = n / 1024, TE = tw_block_entries<L>();
+    __shared__ typename F::T tws[TE];
+    __shared__ V lds[W][kBlkWords];
+    const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
+    F::with(c, limb, [&](const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        tw_stage<L, 1>(tws, f.tw, blk);
+        __syncthreads();
+        const TW tw{f.tw, tws, (uint32_t)blk};
+        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W) {
+            const uint32_t tid = 64u * blk + fresh(lane);
+            uint64_t *row = X + (item * 2 * K + limb) * (size_t)n;
+            V x[2][16];
+            load_block<L, Fd>(x[0], row, tid);
+            load_block<L, Fd>(x[1], row + (size_t)K * n, tid);
+            f.enter_block(x);
+            fwd_block_pair<L>(x, lds[w], lane, (int)tid, f, tw);
+            f.operands(x);
+            // lane order: only k_split_pre2 reads these
+#pragma unroll
+            for (int p = 0; p < 2; p++)
+#pragma unroll
+                for (int s = 0; s < 16; s++)
+                    row[(size_t)p * K * n + blk * 1024u + s * 64u + lane] = Fd::to_bits(x[p][s]);
+        }
+    });
+}
+
+template <int L, class F, int W>
+__global__ __launch_bounds__(64 * W) void k_split_pre2(DevCtx c, const uint64_t *__restrict__ Ahat, size_t na,
+                                                       size_t item0, const uint64_t *__restrict__ Bhat,
+                                                       uint64_t *__restrict__ Dt, size_t items) {
+    typedef typename F::V V;
+    typedef TwBlock<typename F::T> TW;
+    constexpr int n = Geo<L>::N, NB = n / 1024, TE = tw_block_entries<L>(), LAST = Geo<L>::NPASS - 1;
+    __shared__ typename F::T tws[TE];
+    __shared__ V lds[W][kBlkWords];
+    const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
+    const size_t rs = (size_t)K * n;
+    F::with(c, limb, [&](const auto &f) {
+        typedef std::decay_t<decltype(f)> Fd;
+        tw_stage<L, 1>(tws, f.itw, blk);
+        __syncthreads();
+        const TW itw{f.itw, tws, (uint32_t)blk};
+        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W) {
+            const uint32_t tid = 64u * blk + fresh(lane);
+            const size_t o = (size_t)limb * n + blk * 1024u + fresh(lane);
+            const uint64_t *a = Ahat + ((item0 + item) % na) * 2 * rs + o, *b = Bhat + (item0 + item) * 2 * rs + o;
+            V x[2][16], z[1][16];
+#pragma unroll
+            for (int s = 0; s < 16; s++) {
+                const V a0 = Fd::from_bits(a[s * 64]), a1 = Fd::from_bits(a[rs + s * 64]);
+                const V b0 = Fd::from_bits(b[s * 64]), b1 = Fd::from_bits(b[rs + s * 64]);
+                x[0][s] = f.mul(a0, b0);
+                z[0][s] = f.add2(f.mul(a0, b1), f.mul(a1, b0));
+                x[1][s] = f.mul(a1, b1);
+                if constexpr (serial<Fd, TW>()) __builtin_amdgcn_sched_barrier(0);
+            }
+            asm volatile("" ::: "memory");
+            uint64_t *dst = Dt + (item * 3 * K + limb) * (size_t)n;
+            inv_block_pair<L>(x, lds[w], lane, (int)tid, f, itw);
+            store_block<L, Fd>(dst, x[0], tid);
+            store_block<L, Fd>(dst + 2 * rs, x[1], tid);
+            asm volatile("" ::: "memory");
+            inv_block<L, LAST, 1>(z, lds[w], lane, (int)tid, f, itw);
+            store_block<L, Fd>(dst + rs, z[0], tid);
+        }
+    });
+}
+
 // grid (column groups, 3 K, items): rows of Dt [item][comp][limb], in place.
 template <int L, class F>
 __global__ __launch_bounds__(kColThreads) void k_split_inv(DevCtx c, uint64_t *__restrict__ Dt) {
@@ -695,6 +775,31 @@ struct SplitL {
             }
         });
     }
+    // W waves per workgroup: as many as share a CU where the blocks fill it,
+    // fewer for small launches, which then spread over more CUs.
+    static hipError_t fwd_blocks(const DevCtx &c, uint64_t *X, size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            typedef decltype(fam) F;
+            if (items * c.K * NB <= kFewBlocks)
+                hipLaunchKernelGGL((k_split_ops<L, F, 4>), dim3(c.K * NB, (unsigned)((items + 3) / 4)), dim3(256), 0,
+                                   s, c, X, items);
+            else
+                hipLaunchKernelGGL((k_split_ops<L, F, 12>), many_grid<12>(c.K * NB, items), dim3(768), 0, s, c, X,
+                                   items);
+        });
+    }
+    static hipError_t pre2(const DevCtx &c, const uint64_t *Ahat, size_t na, size_t item0, const uint64_t *Bhat,
+                           uint64_t *Dt, size_t items, hipStream_t s) {
+        return tensor_field(c, [&](auto fam) {
+            typedef decltype(fam) F;
+            if (items * c.K * NB <= kFewBlocks)
+                hipLaunchKernelGGL((k_split_pre2<L, F, 4>), dim3(c.K * NB, (unsigned)((items + 3) / 4)), dim3(256), 0,
+                                   s, c, Ahat, na, item0, Bhat, Dt, items);
+            else
+                hipLaunchKernelGGL((k_split_pre2<L, F, 12>), many_grid<12>(c.K * NB, items), dim3(768), 0, s, c, Ahat,
+                                   na, item0, Bhat, Dt, items);
+        });
+    }
     static hipError_t inv(const DevCtx &c, uint64_t *Dt, size_t items, hipStream_t s) {
         return tensor_field(c, [&](auto fam) {
             hipLaunchKernelGGL((k_split_inv<L, decltype(fam)>), dim3(CG, 3 * c.K, (unsigned)items), dim3(kColThreads),
@@ -781,6 +886,7 @@ struct SplitL {
 #define FHE_CAT(a, b) FHE_CAT2(a, b)
 const SplitOps *FHE_CAT(split_ops_, FHE_NTT_L)() {
     typedef SplitL<FHE_NTT_L> S;
-    static const SplitOps o = {S::lift_fwd, S::fwd, S::blocks, S::inv, S::inv_scale, S::digits, S::relin};
+    static const SplitOps o = {S::lift_fwd, S::fwd,       S::blocks, S::fwd_blocks, S::pre2,
+                               S::inv,      S::inv_scale, S::digits, S::relin};
     return &o;
 }

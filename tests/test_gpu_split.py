@@ -76,3 +76,49 @@ def test_products_and_squares(n, bits, t, many):
             g = fhe.to_numpy_u64(got)
             for j in range(g.shape[0]):
                 assert (g[j] == want[j % 3]).all(), (fused, g.shape[0], j)
+
+
+@pytest.mark.parametrize("n,bits,ncls,count,nbits", [(256, (55, 55), 4, 2, 3), (4096, (36, 36, 36), 3, 5, 2),
+                                                     (256, (40, 40, 40), 2, 3, 1), (256, (30,), 5, 1, 4)])
+def test_comparisons_batched_or_in_turn(n, bits, ncls, count, nbits):
+    """fhe_argmax and fhe_less_than give the same words with the bits and pairs
+    side by side as one after the other (a workspace that only holds that), and
+    with room for some of the pairs; sampled items equal the oracle."""
+    import ctypes
+    import torch
+    qs = primes(n, bits)
+    k = len(qs)
+    print(f"[gpu-split] argmax n={n} ncls={ncls} count={count} nbits={nbits}", flush=True)
+    P = bfv.Params(n, qs, 17, "coeff")
+    km = inputs.key_material(n, qs, 6)
+    _, rlk = bfv.keygen(P, km["s"], km["pk_a"], km["pk_e"], km["rlk_a"], km["rlk_e"])
+    ctx = fhe.Context(n, qs, 17, "coeff")
+    rlk_d = ctx.rlk_import(up(rlk))
+    sc = inputs.uniform_ciphertexts(n, qs, ncls * count * nbits, 8).reshape(ncls, count, nbits, 2, k, n)
+    d = up(sc)
+    L = fhe.lib()
+    ctb = 2 * k * n * 8
+    mul = L.fhe_workspace_bytes(ctx._h, fhe.OP_MUL_RELIN, count)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def argmax(bytes_):
+        ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+        out = torch.empty((ncls, count, 2, k, n), dtype=torch.int64, device="cuda")
+        st = L.fhe_argmax(ctx._h, rlk_d.data_ptr(), d.data_ptr(), ncls, nbits, out.data_ptr(), count, ws.data_ptr(),
+                          bytes_, stream)
+        return st, fhe.to_numpy_u64(out)
+
+    whole = fhe.to_numpy_u64(ctx.argmax(rlk_d, d))
+    in_turn = 8 * count * ctb + mul  # the least that was ever asked for
+    need = L.fhe_workspace_bytes(ctx._h, fhe.OP_ARGMAX, count)
+    assert in_turn <= need
+    for b in (in_turn, (in_turn + need) // 2 // 256 * 256, need, 4 * need):
+        st, got = argmax(b)
+        assert st == 0 and (got == whole).all(), b
+    assert argmax(in_turn - 256)[0] == -8
+    lt = fhe.to_numpy_u64(ctx.less_than(rlk_d, d[0].contiguous(), d[1].contiguous()))
+    for j in {0, count - 1}:
+        assert (lt[j] == bfv.less_than(P, rlk, list(sc[0, j]), list(sc[1, j]))).all(), j
+        want = bfv.argmax(P, rlk, [list(sc[c, j]) for c in range(ncls)])
+        for c in range(ncls):
+            assert (whole[c, j] == want[c]).all(), (j, c)
