@@ -267,6 +267,7 @@ struct fhe_ctx {
     // pinned staging of fhe_weighted_sum's weights; the event marks the end of
     // the last copy out of it
     int32_t *wpin = nullptr;
+    void *wpin_dev = nullptr;  // its address on the device
     size_t wpin_cap = 0;
     hipEvent_t wpin_ev = nullptr;
 };
@@ -827,6 +828,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
         P.r32 = (uint64_t)(((u128)1 << 32) % q);
         P.r32_p = shoup(P.r32, q);
         P.mx_neg_bias = (q - (uint64_t)(((u128)FHE_MX_BIAS * 0x0101010101010101ull) % q)) % q;
+        P.r128 = mont(mont(1, q), q);
         P.c96 = q > (1ull << 33) ? (uint64_t)(((u128)1 << 96) / q) : 0;
         P.off59 = ((1ull << 59) + q - 1) / q * q;
         P.off62 = ((1ull << 62) + q - 1) / q * q;
@@ -1830,6 +1832,7 @@ static fhe_status pinned_stage(fhe_ctx *c, size_t words) {
             c->wpin = nullptr;
             return FHE_ENOMEM;
         }
+        FHE_HIP(hipHostGetDevicePointer(&c->wpin_dev, c->wpin, 0));
         c->wpin_cap = words;
     }
     return FHE_OK;
@@ -1842,7 +1845,7 @@ static fhe_status stage_weights(fhe_ctx *c, const int32_t *w, size_t nout, size_
     FHE_TRY(pinned_stage(c, words));
     std::memset(c->wpin, 0, words * 4);
     for (size_t m = 0; m < nout; m++) std::memcpy(c->wpin + m * stride, w + m * nin, nin * 4);
-    FHE_HIP(hipMemcpyAsync(dst, c->wpin, words * 4, hipMemcpyHostToDevice, st));
+    FHE_HIP(launch_copy_words(c->wpin_dev, dst, words, st));
     FHE_HIP(hipEventRecord(c->wpin_ev, st));
     return FHE_OK;
 }
@@ -1853,7 +1856,7 @@ static fhe_status stage_weights_mx(fhe_ctx *c, const int32_t *w, size_t nout, si
     const size_t bytes = weighted_sum_mx_bytes(nout, nin);
     FHE_TRY(pinned_stage(c, (bytes + 3) / 4));
     weighted_sum_mx_table(w, nout, nin, (int8_t *)c->wpin);
-    FHE_HIP(hipMemcpyAsync(dst, c->wpin, bytes, hipMemcpyHostToDevice, st));
+    FHE_HIP(launch_copy_words(c->wpin_dev, dst, bytes / 4, st));
     FHE_HIP(hipEventRecord(c->wpin_ev, st));
     return FHE_OK;
 }

@@ -185,6 +185,9 @@ hipError_t launch_bridge_combine(const DevCtx &c, const uint64_t *y, uint64_t *b
 // out = sum_b 2^b bits[b] by Horner; signed_top: the leading bit weighs -2^(nbits-1)
 hipError_t launch_horner(const DevCtx &c, const uint64_t *bits, int nbits, uint64_t *out,
                          size_t count, int signed_top, hipStream_t s);
+// dst := src, 32-bit words; src may be pinned host memory (a copy of a few KiB
+// between kernels of one stream: the copy engine costs about 15 us of hand-over)
+hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s);
 // Comparisons of up to kLtPairs pairs of bit vectors (k_lt_step, k_argmax_factor).
 constexpr int kLtPairs = 16;
 struct LtPairs {

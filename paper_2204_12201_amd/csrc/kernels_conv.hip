@@ -188,20 +188,12 @@ __global__ __launch_bounds__(256) void k_scale(DevCtx c, const uint64_t *__restr
 // gamma table per chain and prime l of Q then P: [2 gamma 2^64 mod p_l,
 // gamma^2 mod p_l] (the first a Montgomery multiplier).
 
-// (hi 2^64 + lo) mod p for p < 2^62, by 64 doubling steps (setup only).
-__device__ uint64_t mod128_slow(uint64_t hi, uint64_t lo, uint64_t p) {
-    uint64_t r = hi % p;
-    for (int b = 63; b >= 0; b--) {
-        r = (r << 1) | ((lo >> b) & 1u);
-        if (r >= p) r -= p;
-    }
-    return r;
-}
-
-__device__ uint64_t mulmod_slow(uint64_t a, uint64_t b, uint64_t p) {
-    uint64_t lo, hi;
-    mul128(a, b, lo, hi);
-    return mod128_slow(hi, lo, p);
+// [2 gamma 2^64 mod p, gamma^2 mod p] from gamma in [0, p): products by
+// 2^128 mod p and by gamma, each with a factor 2^-64.
+__device__ __forceinline__ void gamma_pair(uint64_t gm, const PrimeConst &P, uint64_t *g) {
+    const uint64_t p = P.q, m = csub(mont_mul_lazy(gm, P.r128, p, P.qinv_neg), p);  // gamma 2^64
+    g[0] = add_mod(m, m, p);
+    g[1] = csub(mont_mul_lazy(m, gm, p, P.qinv_neg), p);
 }
 
 // One thread per chain (input j = chain / tcount, c = c0 + chain % tcount).
@@ -227,17 +219,13 @@ __global__ __launch_bounds__(64) void k_bridge_gamma(DevCtx c, const uint64_t *_
             const uint64_t dc = mul_shoup(cv % q, cc.delta_q[i], cc.delta_qs[i], q);
             x0[i] = sub_mod(x[(j * 2) * (size_t)k * n + (size_t)i * n], dc, q);
             const uint64_t gm = dc ? q - dc : 0;  // gamma mod q_i = -Delta c
-            const uint64_t r1 = (uint64_t)0 - cc.q_one[i] * q;  // 2^64 mod q (< q)
-            g[2 * i] = mulmod_slow(add_mod(gm, gm, q), r1, q);
-            g[2 * i + 1] = mulmod_slow(gm, gm, q);
+            gamma_pair(gm, c.pc[i], g + 2 * i);
         }
     }
     lift_coef<MK, MKP, EX>(c, x0, [&](int jp, uint64_t r) {
         const uint64_t p = cc.p[jp];
         const uint64_t gm = sub_mod(r, E[(j * 2) * (size_t)K * n + (size_t)(k + jp) * n], p);
-        const uint64_t r1 = (uint64_t)0 - cc.p_one[jp] * p;
-        g[2 * (k + jp)] = mulmod_slow(add_mod(gm, gm, p), r1, p);
-        g[2 * (k + jp) + 1] = mulmod_slow(gm, gm, p);
+        gamma_pair(gm, c.pc[k + jp], g + 2 * (k + jp));
     });
     (void)kp;
 }
@@ -528,6 +516,11 @@ __global__ __launch_bounds__(256) void k_argmax_factor(DevCtx c, const uint64_t 
     const uint64_t v = lt[(pair * count + j) * W + p];
     const uint64_t one = p < (uint32_t)(c.k * c.n) && (p & (c.n - 1)) == 0 ? c.cc->delta_q[limb] : 0;
     out[(size_t)y * W + p] = o < cl ? v : sub_mod(one, v, q);
+}
+
+__global__ __launch_bounds__(256) void k_copy_words(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst,
+                                                    size_t words) {
+    for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
 __global__ void k_validate(DevCtx c, const uint64_t *__restrict__ a, size_t words, int kmod, int off,
@@ -983,6 +976,13 @@ hipError_t launch_horner(const DevCtx &c, const uint64_t *bits, int nbits, uint6
     const size_t words = count * 2 * c.k * (size_t)c.n;
     if (words == 0) return hipSuccess;
     hipLaunchKernelGGL(k_horner, dim3(grid_for(words)), dim3(256), 0, s, c, bits, nbits, out, count, signed_top);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s) {
+    if (words == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_copy_words, dim3(grid_for(words)), dim3(256), 0, s, (const uint32_t *)src, (uint32_t *)dst,
+                       words);
     return hipGetLastError();
 }
 

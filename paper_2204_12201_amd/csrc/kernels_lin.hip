@@ -15,6 +15,8 @@
 // The kernel is bound by writing the outputs (one word per output per input
 // word position); the inputs of a position are read once per block of WS_M
 // outputs and stay in the L2 / last-level cache between blocks.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "modarith.hpp"
 #include "ntt_core.hpp"
@@ -145,8 +147,11 @@ __global__ __launch_bounds__(256) void k_weighted_sum(DevCtx c, const uint64_t *
 
 typedef int ws_v4i __attribute__((ext_vector_type(4)));
 
-// Waves per workgroup of the matrix-core weighted sum (each a tile of 16 word positions).
+// Waves per workgroup of the matrix-core weighted sum (each a tile of 16 word
+// positions) and tiles of 16 outputs staged in LDS at a time (32 KiB: four
+// workgroups share a CU, as many as the registers allow).
 constexpr int WSX_WAVES = 4;
+constexpr int WSX_TILES = 32;
 
 __device__ __forceinline__ uint64_t ws_digits(uint64_t x) {
     constexpr uint64_t B = 0x8080808080808080ull;
@@ -174,17 +179,22 @@ __device__ __forceinline__ uint64_t wsx_reduce(uint64_t hi, uint64_t lo, uint64_
 }
 
 // Wave w of workgroup x takes word positions p0 = 16 (WSX_WAVES x + w) .. p0 + 15
-// (input j at in + j in_js, output m at out + m out_ms) for the output tiles
-// blockIdx.y, blockIdx.y + gridDim.y, ... < nmt; wt: the pass's A operands
-// [nmt][64] (16 bytes each); accumulate: add into out.
-__global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, const uint64_t *__restrict__ in, size_t in_js,
-                                                         int nj, const ws_v4i *__restrict__ wt, int nmt,
-                                                         size_t nout, uint64_t *__restrict__ out, size_t out_ms,
-                                                         int accumulate) {
+// (input j at in + j in_js, output m at out + m out_ms) for its share
+// (blockIdx.y of gridDim.y) of the nmt output tiles; wt: the pass's A operands
+// [nmt][64] (16 bytes each); ACC: add into out.
+template <bool ACC>
+__global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, const uint64_t *__restrict__ in,
+                                                                    size_t in_js, int nj,
+                                                                    const ws_v4i *__restrict__ wt, int nmt,
+                                                                    size_t nout, uint64_t *__restrict__ out,
+                                                                    size_t out_ms) {
     const size_t W = (size_t)2 * c.k * c.n;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, col = lane & 15u, g = lane >> 4;
-    const size_t p0 = ((size_t)blockIdx.x * WSX_WAVES + wave) * 16;
-    if (p0 >= W) return;  // whole waves
+    __shared__ ws_v4i sh[WSX_TILES][64];
+    const uint32_t lane = threadIdx.x & 63u, col = lane & 15u, g = lane >> 4;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    size_t p0 = ((size_t)blockIdx.x * WSX_WAVES + wave) * 16;
+    const bool active = p0 < W;  // whole waves; the others only help to stage
+    if (!active) p0 = 0;
     const size_t p = p0 + col;
     const int limb = (int)((p0 >> c.L) % (size_t)c.k);
     // the prime's constants in registers (a store to out could alias the
@@ -205,20 +215,14 @@ __global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, co
         Bu[u] = ws_v4i{(int)ws_gather(d, u), (int)ws_gather(d + 4, u), (int)ws_gather(d + 8, u),
                        (int)ws_gather(d + 12, u)};
     const ws_v4i bias = {FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS};
-    // the next tile's weights are fetched before this tile's stores: vector
-    // memory completes in order, so a load behind them would wait for them
-    ws_v4i An = wt[(size_t)blockIdx.y * 64 + lane];
-    for (int mt = (int)blockIdx.y; mt < nmt; mt += (int)gridDim.y) {
-        const ws_v4i A = An;
-        const int next = mt + (int)gridDim.y;
-        An = wt[(size_t)(next < nmt ? next : mt) * 64 + lane];
+    auto tile = [&](const ws_v4i A, int mt, auto whole) {
         ws_v4i acc[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bu[u], bias, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const size_t m = (size_t)mt * 16 + 4 * g + i;
-            if (m >= nout) continue;
+            if (!decltype(whole)::value && m >= nout) continue;
             const uint32_t a01 = (uint32_t)acc[0][i] + ((uint32_t)acc[1][i] << 8);
             const uint32_t a23 = (uint32_t)acc[2][i] + ((uint32_t)acc[3][i] << 8);
             const uint32_t a45 = (uint32_t)acc[4][i] + ((uint32_t)acc[5][i] << 8);
@@ -228,8 +232,24 @@ __global__ __launch_bounds__(64 * WSX_WAVES) void k_weighted_sum_mx(DevCtx c, co
             const uint64_t hi = (x >> 32) + w + (E >> 32), lo = (x & 0xFFFFFFFFull) + (uint32_t)E;
             uint64_t r = wsx_reduce(hi, lo, q, nq, c96, r32, r32p, onep);
             uint64_t *o = out + m * out_ms + p;
-            if (accumulate) r = add_mod(r, *o, q);
+            if (ACC) r = add_mod(r, *o, q);
             *o = r;
+        }
+    };
+    // The weights come from LDS, WSX_TILES tiles at a time: a vector memory load
+    // per tile completes in order behind the stores of the tile before, so that
+    // every wave waited for its own stores (57 % of the wave time).
+    const int per = (nmt + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int first = (int)blockIdx.y * per, last = first + per < nmt ? first + per : nmt;
+    for (int t0 = first; t0 < last; t0 += WSX_TILES) {
+        const int cnt = last - t0 < WSX_TILES ? last - t0 : WSX_TILES;
+        if (t0 > first) __syncthreads();
+        for (int e = (int)threadIdx.x; e < cnt * 64; e += 64 * WSX_WAVES) sh[e >> 6][e & 63] = wt[(size_t)t0 * 64 + e];
+        __syncthreads();
+        if (!active) continue;
+        for (int t = 0; t < cnt; t++) {
+            if ((size_t)(t0 + t + 1) * 16 <= nout) tile(sh[t][lane], t0 + t, std::true_type());
+            else tile(sh[t][lane], t0 + t, std::false_type());
         }
     }
 }
@@ -266,8 +286,9 @@ hipError_t launch_weighted_sum_mx(const DevCtx &c, const uint64_t *in, size_t ni
     const ws_v4i *wt = (const ws_v4i *)tab;
     for (size_t pp = 0; pp < npass; pp++) {
         const int nj = (int)(nin - pp * 64 < 64 ? nin - pp * 64 : 64);
-        hipLaunchKernelGGL(k_weighted_sum_mx, dim3((unsigned)nbx, (unsigned)gy), dim3(64 * WSX_WAVES), 0, s, c,
-                           in + pp * 64 * W, W, nj, wt + pp * nmt * 64, (int)nmt, nout, out, W, pp > 0 ? 1 : 0);
+        auto kern = pp > 0 ? k_weighted_sum_mx<true> : k_weighted_sum_mx<false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)nbx, (unsigned)gy), dim3(64 * WSX_WAVES), 0, s, c, in + pp * 64 * W, W,
+                           nj, wt + pp * nmt * 64, (int)nmt, nout, out, W);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

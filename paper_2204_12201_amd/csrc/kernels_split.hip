@@ -344,6 +344,7 @@ __global__ __launch_bounds__(256) void k_split_tensor(DevCtx c, const uint64_t *
     constexpr int n = Geo<L>::N, NB = n / 1024, LAST = Geo<L>::NPASS - 1, NP = SQ ? 2 : 4;
     __shared__ V lds[SQ ? 3 : 4][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     const uint32_t tid = 64u * blk + lane;
     const size_t item = blockIdx.y;
@@ -400,13 +401,14 @@ __global__ __launch_bounds__(64 * W) void k_split_tensor_many(DevCtx c, const ui
     __shared__ typename F::T tws[2][TE];
     __shared__ typename F::V lds[W][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         tw_stage<L, 1>(tws[0], f.tw, blk);
         tw_stage<L, 1>(tws[1], f.itw, blk);
         __syncthreads();
-        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W)
+        for (size_t item = blockIdx.y * wpg + w; item < items; item += gridDim.y * wpg)
             tensor_block<L, Fd, SQ>(f, X + (item * (SQ ? 2 : 4) * K + limb) * (size_t)n,
                                     Dt + (item * 3 * K + limb) * (size_t)n, (size_t)K * n, lds[w], lane,
                                     64u * blk + fresh(lane), TW{f.tw, tws[0], (uint32_t)blk},
@@ -426,13 +428,14 @@ __global__ __launch_bounds__(64 * W) void k_split_ops(DevCtx c, uint64_t *__rest
     __shared__ typename F::T tws[TE];
     __shared__ V lds[W][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     F::with(c, limb, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
         tw_stage<L, 1>(tws, f.tw, blk);
         __syncthreads();
         const TW tw{f.tw, tws, (uint32_t)blk};
-        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W) {
+        for (size_t item = blockIdx.y * wpg + w; item < items; item += gridDim.y * wpg) {
             const uint32_t tid = 64u * blk + fresh(lane);
             uint64_t *row = X + (item * 2 * K + limb) * (size_t)n;
             V x[2][16];
@@ -461,6 +464,7 @@ __global__ __launch_bounds__(64 * W) void k_split_pre2(DevCtx c, const uint64_t 
     __shared__ typename F::T tws[TE];
     __shared__ V lds[W][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     const size_t rs = (size_t)K * n;
     F::with(c, limb, [&](const auto &f) {
@@ -468,7 +472,7 @@ __global__ __launch_bounds__(64 * W) void k_split_pre2(DevCtx c, const uint64_t 
         tw_stage<L, 1>(tws, f.itw, blk);
         __syncthreads();
         const TW itw{f.itw, tws, (uint32_t)blk};
-        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W) {
+        for (size_t item = blockIdx.y * wpg + w; item < items; item += gridDim.y * wpg) {
             const uint32_t tid = 64u * blk + fresh(lane);
             const size_t o = (size_t)limb * n + blk * 1024u + fresh(lane);
             const uint64_t *a = Ahat + ((item0 + item) % na) * 2 * rs + o, *b = Bhat + (item0 + item) * 2 * rs + o;
@@ -658,6 +662,7 @@ __global__ __launch_bounds__(64 * W) void k_split_relin_many(DevCtx c, const uin
     __shared__ typename F::T tws[2][TE];
     __shared__ V lds[W][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int j = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, k = c.k;
     F::with(c, j, [&](const auto &f) {
         typedef std::decay_t<decltype(f)> Fd;
@@ -665,7 +670,7 @@ __global__ __launch_bounds__(64 * W) void k_split_relin_many(DevCtx c, const uin
         tw_stage<L, 1>(tws[1], f.itw, blk);
         __syncthreads();
         const TW tw{f.tw, tws[0], (uint32_t)blk}, itw{f.itw, tws[1], (uint32_t)blk};
-        for (size_t item = (size_t)blockIdx.y * W + w; item < items; item += (size_t)gridDim.y * W) {
+        for (size_t item = blockIdx.y * wpg + w; item < items; item += gridDim.y * wpg) {
             const uint32_t tid = 64u * blk + fresh(lane);
             V acc[2][16];
             zero2(acc);
@@ -722,10 +727,17 @@ constexpr size_t kFewBlocks = 3072;
 
 // A workgroup of W waves fills a CU (its LDS): item groups for about one
 // workgroup per CU, which then keeps its twiddles and its waves until the end.
+// Its waves: W, or as many as give every wave of every group the same number of
+// items (16 items of key switching at n = 16384 on two groups: eight waves each,
+// not twelve and four).
+struct ManyShape {
+    dim3 grid, block;
+};
 template <int W>
-dim3 many_grid(size_t cols, size_t items) {
-    const size_t most = (items + W - 1) / W, fit = cols < 256 ? 256 / cols : 1;
-    return dim3((unsigned)cols, (unsigned)(fit < most ? fit : most));
+ManyShape many_shape(size_t cols, size_t items) {
+    const size_t most = (items + W - 1) / W, fit = cols < 256 ? 256 / cols : 1, y = fit < most ? fit : most;
+    const size_t per = (items + y - 1) / y, rounds = (per + W - 1) / W, waves = (per + rounds - 1) / rounds;
+    return {dim3((unsigned)cols, (unsigned)y), dim3((unsigned)(64 * waves))};
 }
 
 // ---- launches --------------------------------------------------------------------
@@ -767,11 +779,11 @@ struct SplitL {
                 if (sq) hipLaunchKernelGGL((k_split_tensor<L, F, true>), grid, dim3(192), 0, s, c, X, Dt);
                 else hipLaunchKernelGGL((k_split_tensor<L, F, false>), grid, dim3(256), 0, s, c, X, Dt);
             } else if (sq) {
-                hipLaunchKernelGGL((k_split_tensor_many<L, F, true, W>), many_grid<W>(c.K * NB, items), dim3(64 * W),
-                                   0, s, c, X, Dt, items);
+                const ManyShape g = many_shape<W>(c.K * NB, items);
+                hipLaunchKernelGGL((k_split_tensor_many<L, F, true, W>), g.grid, g.block, 0, s, c, X, Dt, items);
             } else {
-                hipLaunchKernelGGL((k_split_tensor_many<L, F, false, W>), many_grid<W>(c.K * NB, items), dim3(64 * W),
-                                   0, s, c, X, Dt, items);
+                const ManyShape g = many_shape<W>(c.K * NB, items);
+                hipLaunchKernelGGL((k_split_tensor_many<L, F, false, W>), g.grid, g.block, 0, s, c, X, Dt, items);
             }
         });
     }
@@ -780,24 +792,27 @@ struct SplitL {
     static hipError_t fwd_blocks(const DevCtx &c, uint64_t *X, size_t items, hipStream_t s) {
         return tensor_field(c, [&](auto fam) {
             typedef decltype(fam) F;
-            if (items * c.K * NB <= kFewBlocks)
+            if (items * c.K * NB <= kFewBlocks) {
                 hipLaunchKernelGGL((k_split_ops<L, F, 4>), dim3(c.K * NB, (unsigned)((items + 3) / 4)), dim3(256), 0,
                                    s, c, X, items);
-            else
-                hipLaunchKernelGGL((k_split_ops<L, F, 12>), many_grid<12>(c.K * NB, items), dim3(768), 0, s, c, X,
-                                   items);
+            } else {
+                const ManyShape g = many_shape<12>(c.K * NB, items);
+                hipLaunchKernelGGL((k_split_ops<L, F, 12>), g.grid, g.block, 0, s, c, X, items);
+            }
         });
     }
     static hipError_t pre2(const DevCtx &c, const uint64_t *Ahat, size_t na, size_t item0, const uint64_t *Bhat,
                            uint64_t *Dt, size_t items, hipStream_t s) {
         return tensor_field(c, [&](auto fam) {
             typedef decltype(fam) F;
-            if (items * c.K * NB <= kFewBlocks)
+            if (items * c.K * NB <= kFewBlocks) {
                 hipLaunchKernelGGL((k_split_pre2<L, F, 4>), dim3(c.K * NB, (unsigned)((items + 3) / 4)), dim3(256), 0,
                                    s, c, Ahat, na, item0, Bhat, Dt, items);
-            else
-                hipLaunchKernelGGL((k_split_pre2<L, F, 12>), many_grid<12>(c.K * NB, items), dim3(768), 0, s, c, Ahat,
-                                   na, item0, Bhat, Dt, items);
+            } else {
+                const ManyShape g = many_shape<12>(c.K * NB, items);
+                hipLaunchKernelGGL((k_split_pre2<L, F, 12>), g.grid, g.block, 0, s, c, Ahat, na, item0, Bhat, Dt,
+                                   items);
+            }
         });
     }
     static hipError_t inv(const DevCtx &c, uint64_t *Dt, size_t items, hipStream_t s) {
@@ -828,8 +843,8 @@ struct SplitL {
                 hipLaunchKernelGGL((k_split_relin<L, F>), dim3((unsigned)k * NB, (unsigned)items), dim3(64 * W),
                                    (W * kBlkWords + 2048) * 8, s, c, D, rlk, R);
             } else {
-                hipLaunchKernelGGL((k_split_relin_many<L, F, WM>), many_grid<WM>(k * NB, items), dim3(64 * WM), 0, s,
-                                   c, D, rlk, R, items);
+                const ManyShape g = many_shape<WM>(k * NB, items);
+                hipLaunchKernelGGL((k_split_relin_many<L, F, WM>), g.grid, g.block, 0, s, c, D, rlk, R, items);
             }
             hipLaunchKernelGGL((k_split_fin<L, F>), dim3(CG, 2 * (unsigned)k, (unsigned)items), dim3(kColThreads), 0,
                                s, c, R, out);

@@ -23,6 +23,7 @@ struct PrimeConst {
     // primes below 2^50 (ntt_field.hpp): p, 1/p, and with their quotients by p
     // the centred constants n^-1 and 2^-64 mod p
     double pf, pinvf, ninvf, ninvf_i, m64f, m64f_i;
+    uint64_t r128;             // 2^128 mod q (to Montgomery form)
     uint64_t c96;              // floor(2^96 / q) for q > 2^33, else 0 (quotients of the weighted sums)
     uint64_t mx_neg_bias;      // -FHE_MX_BIAS sum_{u < 8} 256^u mod q (matrix-core weighted sums)
 };
