@@ -194,20 +194,20 @@ typedef MxSharedT<3, kMxSpan> MxShared;
 // acc[mm] = FHE_MX_BIAS + A[mm] B, mm = 0..3 (A = table `t` of the LDS): lane
 // gets P' of target l/16 (acc[0]: digits 0..3, acc[1]: 4..7) and of target
 // l/16 + 4 (acc[2], acc[3]).
-template <class Sh>
+template <int H = 2, class Sh>
 __device__ __forceinline__ void mx_products(const Sh &sh, int t, uint32_t lane, const mx_v4i B,
                                             mx_v4i (&acc)[4]) {
     const mx_v4i bias = {FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS, FHE_MX_BIAS};
 #pragma unroll
-    for (int mm = 0; mm < 4; mm++) acc[mm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sh.a[t][mm][lane], B, bias, 0, 0, 0);
+    for (int mm = 0; mm < 2 * H; mm++) acc[mm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sh.a[t][mm][lane], B, bias, 0, 0, 0);
 }
 
 // acc[mm] += A[mm] B (table `t`): a second block of 64 (source, digit) pairs.
-template <class Sh>
+template <int H = 2, class Sh>
 __device__ __forceinline__ void mx_products_add(const Sh &sh, int t, uint32_t lane, const mx_v4i B,
                                                 mx_v4i (&acc)[4]) {
 #pragma unroll
-    for (int mm = 0; mm < 4; mm++)
+    for (int mm = 0; mm < 2 * H; mm++)
         acc[mm] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sh.a[t][mm][lane], B, acc[mm], 0, 0, 0);
 }
 
@@ -331,21 +331,24 @@ __device__ __forceinline__ void mx_stage_scale_slots(Sh &sh, const DevCtx &c) {
     }
 }
 
+// H: slots per lane (1 where both bases have at most 4 primes: half the products
+// and half the lanes' arithmetic; slots g + 4h, h < H).
+//
 // Scale-and-round of one tile column on the matrix cores (tables 0: scale in
 // P from the y_i, 1: P -> Q, 2: scale in P from D_p, block-diagonal).  dq,
 // dp: the lane's two Q and two P residues of D, any representatives below
 // 2^62 (absent primes read a present row; their constants and weights are
 // zero); jv[h]: slot g + 4h is a P prime.  Returns false when the coefficient must take the exact path, else
 // the lane's two outputs C mod q_s in out.
-template <class Sh>
+template <int H = 2, class Sh>
 __device__ __forceinline__ bool mx_scale_tile(const Sh &sh, uint32_t lane, int a16, int a32,
-                                              const uint64_t (&dq)[2], const uint64_t (&dp)[2], const bool (&jv)[2],
-                                              uint64_t (&out)[2]) {
+                                              const uint64_t (&dq)[H], const uint64_t (&dp)[H], const bool (&jv)[H],
+                                              uint64_t (&out)[H]) {
     const uint32_t g = lane >> 4;
-    uint64_t y[2];
+    uint64_t y[H];
     double e = 0.0;
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const uint64_t *Q = sh.cq[g + 4 * h];
         y[h] = add_mod(mul_shoup(dq[h], Q[2], Q[3], Q[0]), Q[4], Q[0]);
         e = fma((double)y[h], mx_f64(Q[7]), e);
@@ -355,12 +358,12 @@ __device__ __forceinline__ bool mx_scale_tile(const Sh &sh, uint32_t lane, int a
     bool exact = (d < FHE_EST_MARGIN) || (d > 1.0 - FHE_EST_MARGIN);
     const uint64_t v = (uint32_t)fl;  // < k
     mx_v4i acc[4];
-    mx_products(sh, 0, lane, mx_operand(y[0], y[1]), acc);
-    mx_products_add(sh, 2, lane, mx_operand(dp[0], dp[1]), acc);
-    uint64_t z[2];
+    mx_products<H>(sh, 0, lane, mx_operand(y[0], H == 2 ? y[H - 1] : 0), acc);
+    mx_products_add<H>(sh, 2, lane, mx_operand(dp[0], H == 2 ? dp[H - 1] : 0), acc);
+    uint64_t z[H];
     double e2 = 0.0;
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const uint64_t *Pc = sh.cp[g + 4 * h];
         uint64_t lo, hi;
         mx_recombine(acc[2 * h], acc[2 * h + 1], lo, hi);
@@ -374,9 +377,9 @@ __device__ __forceinline__ bool mx_scale_tile(const Sh &sh, uint32_t lane, int a
     const double fl2 = floor(e2), d2 = e2 - fl2;
     exact = exact || (fabs(d2 - 0.5) < FHE_EST_MARGIN);
     const uint64_t beta = (uint32_t)fl2 + (d2 > 0.5 ? 1u : 0u);  // <= k'
-    mx_products(sh, 1, lane, mx_operand(z[0], z[1]), acc);
+    mx_products<H>(sh, 1, lane, mx_operand(z[0], H == 2 ? z[H - 1] : 0), acc);
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const uint64_t *Q = sh.cq[g + 4 * h];
         uint64_t lo, hi;
         mx_recombine(acc[2 * h], acc[2 * h + 1], lo, hi);
@@ -420,14 +423,14 @@ __device__ __forceinline__ void mx_stage_lift_slots(Sh &sh, const DevCtx &c) {
 // Centred lift of one tile column on the matrix cores (table 0): x the lane's
 // two Q residues.  Returns false when the coefficient must take the exact
 // path, else the lane's two residues modulo P in out.
-template <class Sh>
+template <int H = 2, class Sh>
 __device__ __forceinline__ bool mx_lift_tile(const Sh &sh, uint32_t lane, int a16, int a32,
-                                             const uint64_t (&x)[2], uint64_t (&out)[2]) {
+                                             const uint64_t (&x)[H], uint64_t (&out)[H]) {
     const uint32_t g = lane >> 4;
-    uint64_t yv[2];
+    uint64_t yv[H];
     double e = 0.0;
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const uint64_t *Q = sh.cq[g + 4 * h];
         yv[h] = mul_shoup(x[h], Q[1], Q[2], Q[0]);
         e = fma((double)yv[h], mx_f64(Q[3]), e);
@@ -436,10 +439,10 @@ __device__ __forceinline__ bool mx_lift_tile(const Sh &sh, uint32_t lane, int a1
     const double fl = floor(e), d = e - fl;
     const uint64_t beta = (uint32_t)fl + (d > 0.5 ? 1u : 0u);  // <= k
     mx_v4i acc[4];
-    mx_products(sh, 0, lane, mx_operand(yv[0], yv[1]), acc);
+    mx_products<H>(sh, 0, lane, mx_operand(yv[0], H == 2 ? yv[H - 1] : 0), acc);
     if (fabs(d - 0.5) < FHE_EST_MARGIN) return false;
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const uint64_t *Pc = sh.cp[g + 4 * h];
         uint64_t lo, hi;
         mx_recombine(acc[2 * h], acc[2 * h + 1], lo, hi);

@@ -66,7 +66,7 @@ __device__ __forceinline__ void col_units(const DevCtx &c, int first, int step, 
 // Lift of the inputs and pass 0 of their forward transforms: grid (n/16/C,
 // npoly, items).  The Q rows go straight through pass 0, the lifted P rows
 // through LDS.
-template <int L, class F, int C, int W>
+template <int L, class F, int C, int W, int H>
 __global__ __launch_bounds__(64 * W) void k_col_lift(DevCtx c, const uint64_t *__restrict__ a,
                                                      const uint64_t *__restrict__ b, uint64_t *__restrict__ X,
                                                      int npoly) {
@@ -84,20 +84,22 @@ __global__ __launch_bounds__(64 * W) void k_col_lift(DevCtx c, const uint64_t *_
     if (threadIdx.x == 0) sh.mx.count = 0;
     __syncthreads();
     const int a16 = (int)((lane ^ 16u) << 2), a32 = (int)((lane ^ 32u) << 2);
-    uint32_t rq[2];
-    bool jv[2];
+    uint32_t rq[H];
+    bool jv[H];
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         rq[h] = mx_row((int)g + 4 * h, k, 0, n);
         jv[h] = (int)g + 4 * h < kp;
     }
     for (int t = w; t < C; t += W) {  // tile: stride e, 16 columns
         const int e = t / (C / 16), cc = t % (C / 16) * 16 + (int)col;
         const uint64_t *s0 = src + e * T + c0 + cc;
-        uint64_t x[2] = {s0[rq[0]], s0[rq[1]]}, r[2];
-        if (mx_lift_tile(sh.mx, lane, a16, a32, x, r)) {
+        uint64_t x[H], r[H];
 #pragma unroll
-            for (int h = 0; h < 2; h++)
+        for (int h = 0; h < H; h++) x[h] = s0[rq[h]];
+        if (mx_lift_tile<H>(sh.mx, lane, a16, a32, x, r)) {
+#pragma unroll
+            for (int h = 0; h < H; h++)
                 if (jv[h]) sh.rows[g + 4 * h][e][cc] = r[h];
         } else if (g == 0) {
             sh.mx.item[atomicAdd(&sh.mx.count, 1)] = e * C + cc;
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(64 * W) void k_col_lift(DevCtx c, const uint64_t *_
 // components 0, 1 into out.  2 + p: component 2 (computed by each of the J
 // parts), whose digits p, p + J, ... of the k^2 (digit, prime) pairs go to D
 // [item][digit][prime] (field DF of the key switching); D null: the component itself to C2 (J = 1).
-template <int L, class F, class DF, bool RAW, int C, int W>
+template <int L, class F, class DF, bool RAW, int C, int W, int H>
 __global__ __launch_bounds__(64 * W) void k_col_scale(DevCtx c, const uint64_t *__restrict__ Dt,
                                                       uint64_t *__restrict__ out, uint64_t *__restrict__ C2,
                                                       uint64_t *__restrict__ D, int J) {
@@ -177,10 +179,10 @@ __global__ __launch_bounds__(64 * W) void k_col_scale(DevCtx c, const uint64_t *
     });
     __syncthreads();
     const int a16 = (int)((lane ^ 16u) << 2), a32 = (int)((lane ^ 32u) << 2);
-    int sq[2], sp[2];
-    bool iv[2], jv[2];
+    int sq[H], sp[H];
+    bool iv[H], jv[H];
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
+    for (int h = 0; h < H; h++) {
         const int s = (int)g + 4 * h;
         iv[h] = s < k;
         jv[h] = s < kp;
@@ -189,12 +191,15 @@ __global__ __launch_bounds__(64 * W) void k_col_scale(DevCtx c, const uint64_t *
     }
     for (int t = w; t < C; t += W) {
         const int e = t / (C / 16), cc = t % (C / 16) * 16 + (int)col;
-        const uint64_t dq[2] = {sh.rows[sq[0]][e][cc], sh.rows[sq[1]][e][cc]};
-        const uint64_t dp[2] = {sh.rows[sp[0]][e][cc], sh.rows[sp[1]][e][cc]};
-        uint64_t r[2];
-        if (mx_scale_tile(sh.mx, lane, a16, a32, dq, dp, jv, r)) {
+        uint64_t dq[H], dp[H], r[H];
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
+        for (int h = 0; h < H; h++) {
+            dq[h] = sh.rows[sq[h]][e][cc];
+            dp[h] = sh.rows[sp[h]][e][cc];
+        }
+        if (mx_scale_tile<H>(sh.mx, lane, a16, a32, dq, dp, jv, r)) {
+#pragma unroll
+            for (int h = 0; h < H; h++) {
                 if (iv[h]) {
                     // a tile's words are read by this wave alone, before it writes them
                     if (digits) sh.rows[g + 4 * h][e][cc] = r[h];
@@ -860,15 +865,31 @@ struct SplitL {
         const size_t lds = sizeof(ColShared<C, NT>) + (size_t)(limbs - 1) * 16 * C * 8;
         hipLaunchKernelGGL(kern, dim3(Geo<L>::T / C, y, (unsigned)items), dim3(64 * W), lds, s, c, args...);
     }
+    template <class F, int H>
+    static void lift_fwd_h(const DevCtx &c, const uint64_t *a, const uint64_t *b, uint64_t *X, int npoly, size_t items,
+                           hipStream_t s) {
+        if (npoly * items * (Geo<L>::T / 64) <= 128)
+            launch_col<16, 8, 1>(k_col_lift<L, F, 16, 8, H>, c, c.kp, npoly, items, s, a, b, X, npoly);
+        else
+            launch_col<64, 8, 1>(k_col_lift<L, F, 64, 8, H>, c, c.kp, npoly, items, s, a, b, X, npoly);
+    }
     static hipError_t lift_fwd(const DevCtx &c, const uint64_t *a, const uint64_t *b, uint64_t *X, int npoly,
                                size_t items, hipStream_t s) {
         return tensor_field(c, [&](auto fam) {
-            typedef decltype(fam) F;
-            if (npoly * items * (Geo<L>::T / 64) <= 128)
-                launch_col<16, 8, 1>(k_col_lift<L, F, 16, 8>, c, c.kp, npoly, items, s, a, b, X, npoly);
-            else
-                launch_col<64, 8, 1>(k_col_lift<L, F, 64, 8>, c, c.kp, npoly, items, s, a, b, X, npoly);
+            if (c.k <= 4 && c.kp <= 4) lift_fwd_h<decltype(fam), 1>(c, a, b, X, npoly, items, s);
+            else lift_fwd_h<decltype(fam), 2>(c, a, b, X, npoly, items, s);
         });
+    }
+    template <class F, class DF, bool RAW, int H>
+    static void inv_scale_h(const DevCtx &c, const uint64_t *Dt, uint64_t *out, uint64_t *C2, uint64_t *D,
+                            size_t items, hipStream_t s) {
+        if (3 * items * (Geo<L>::T / 64) <= 128) {
+            const int J = D && c.k > 3 ? 4 : 1;
+            launch_col<16, 8, 3>(k_col_scale<L, F, DF, RAW, 16, 8, H>, c, c.K, 2 + J, items, s, Dt, out, C2, D, J);
+        } else {
+            constexpr int C = H == 1 ? 64 : 32;  // H = 1: at most 8 rows
+            launch_col<C, 8, 3>(k_col_scale<L, F, DF, RAW, C, 8, H>, c, c.K, 3, items, s, Dt, out, C2, D, 1);
+        }
     }
     static hipError_t inv_scale(const DevCtx &c, const uint64_t *Dt, uint64_t *out, uint64_t *C2, uint64_t *D,
                                 size_t items, hipStream_t s) {
@@ -878,17 +899,8 @@ struct SplitL {
                 typedef decltype(dfam) DF;
                 constexpr bool RAW = decltype(raw)::value;
                 if constexpr (std::is_same<F, FamF>::value == std::is_same<DF, FamF>::value) {
-                    if (3 * items * (Geo<L>::T / 64) <= 128) {
-                        const int J = D && c.k > 3 ? 4 : 1;
-                        launch_col<16, 8, 3>(k_col_scale<L, F, DF, RAW, 16, 8>, c, c.K, 2 + J, items, s, Dt, out, C2,
-                                              D, J);
-                    } else if (c.K <= 8) {
-                        launch_col<64, 8, 3>(k_col_scale<L, F, DF, RAW, 64, 8>, c, c.K, 3, items, s, Dt, out, C2, D,
-                                             1);
-                    } else {
-                        launch_col<32, 8, 3>(k_col_scale<L, F, DF, RAW, 32, 8>, c, c.K, 3, items, s, Dt, out, C2, D,
-                                             1);
-                    }
+                    if (c.k <= 4 && c.kp <= 4) inv_scale_h<F, DF, RAW, 1>(c, Dt, out, C2, D, items, s);
+                    else inv_scale_h<F, DF, RAW, 2>(c, Dt, out, C2, D, items, s);
                 }
             });
         });
