@@ -102,6 +102,9 @@ struct NttOps {
                                   hipStream_t);
     hipError_t (*square_tensor)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, size_t, hipStream_t);
     hipError_t (*relin_fused)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, size_t, hipStream_t);
+    hipError_t (*encrypt_rows)(const DevCtx &, const uint64_t *, const uint64_t *, const int32_t *, const uint64_t *,
+                               uint64_t *, size_t, hipStream_t);
+    hipError_t (*decrypt_rows)(const DevCtx &, const uint64_t *, const uint64_t *, uint64_t *, size_t, hipStream_t);
 };
 hipError_t launch_ntt_rows(const DevCtx &c, uint64_t *data, size_t nrows, int kmod, int limb_off,
                            int mode, hipStream_t s);
@@ -177,9 +180,18 @@ hipError_t launch_pointwise_mont(const DevCtx &c, const uint64_t *a, const uint6
 // out_j = -(prod_j + e_j) + [j == digit] s2_j  (digit < 0: no s^2 term)
 hipError_t launch_key_b(const DevCtx &c, const uint64_t *prod, const uint64_t *e_rns,
                         const uint64_t *s2, int digit, uint64_t *out, hipStream_t s);
-// ct[j] = (prod[0][j] + e[j][0] + Delta m_j, prod[1][j] + e[j][1]); prod [2][count][k][n]
-hipError_t launch_encrypt_finish(const DevCtx &c, const uint64_t *prod, const int32_t *e,
-                                 const uint64_t *pt, uint64_t *ct, size_t count, hipStream_t s);
+// ct[j] = (pk0 u_j + e[j][0] + Delta m_j, pk1 u_j + e[j][1]) from the transforms U
+// [count][k][n] and PK [2][k][n] (kernels_ntt.hip)
+hipError_t launch_encrypt_rows(const DevCtx &c, const uint64_t *U, const uint64_t *PK, const int32_t *e,
+                               const uint64_t *pt, uint64_t *ct, size_t count, hipStream_t s);
+// X[j] = c0 + c1 s of ct[j], S the transform of s (kernels_ntt.hip)
+hipError_t launch_decrypt_rows(const DevCtx &c, const uint64_t *ct, const uint64_t *S, uint64_t *X, size_t count,
+                               hipStream_t s);
+// Host staging in narrow words: dst (64 or 32 bits) := src (32 or 16 bits, pinned
+// host memory) and dst (32 bits, pinned) := src (64 bits)
+hipError_t launch_widen_u32(const uint32_t *src, uint64_t *dst, size_t count, hipStream_t s);
+hipError_t launch_widen_i16(const int16_t *src, int32_t *dst, size_t count, hipStream_t s);
+hipError_t launch_narrow_u32(const uint64_t *src, uint32_t *dst, size_t count, hipStream_t s);
 hipError_t launch_bridge_combine(const DevCtx &c, const uint64_t *y, uint64_t *bits, uint64_t *eq,
                                  size_t count, int tcount, int nbits, int c0, hipStream_t s);
 // out = sum_b 2^b bits[b] by Horner; signed_top: the leading bit weighs -2^(nbits-1)

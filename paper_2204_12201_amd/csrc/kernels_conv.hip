@@ -388,26 +388,9 @@ __global__ void k_key_b(DevCtx c, const uint64_t *__restrict__ prod, const uint6
     }
 }
 
-// ct[j] = (prod[0][j] + e[j][0] + Delta m_j, prod[1][j] + e[j][1]); prod is [2][count][k][n].
-__global__ void k_encrypt_finish(DevCtx c, const uint64_t *__restrict__ prod,
-                                 const int32_t *__restrict__ e, const uint64_t *__restrict__ pt,
-                                 uint64_t *__restrict__ ct, size_t count) {
-    const size_t n = c.n, k = c.k;
-    const size_t total = count * 2 * k * n;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total;
-         i += (size_t)gridDim.x * blockDim.x) {
-        const size_t coef = i % n, limb = (i / n) % k, poly = (i / (n * k)) % 2,
-                     item = i / (2 * n * k);
-        const uint64_t q = c.pc[limb].q;
-        const int64_t ev = e[(item * 2 + poly) * n + coef];
-        const uint64_t er = ev >= 0 ? (uint64_t)ev % q : (q - ((uint64_t)(-ev) % q)) % q;
-        uint64_t r = add_mod(prod[((poly * count + item) * k + limb) * n + coef], er, q);
-        if (poly == 0) {
-            const uint64_t m = pt[item * n + coef] % q;
-            r = add_mod(r, mul_shoup(m, c.cc->delta_q[limb], c.cc->delta_qs[limb], q), q);
-        }
-        ct[i] = r;
-    }
+template <class S, class D>
+__global__ __launch_bounds__(256) void k_convert(const S *__restrict__ src, D *__restrict__ dst, size_t count) {
+    for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) dst[i] = (D)src[i];
 }
 
 // eq_c = Delta [coefficient 0 of c0] - y_c;  bits_b = sum_{c in [1,T), bit b of c} eq_c.
@@ -953,13 +936,20 @@ hipError_t launch_key_b(const DevCtx &c, const uint64_t *prod, const uint64_t *e
     return hipGetLastError();
 }
 
-hipError_t launch_encrypt_finish(const DevCtx &c, const uint64_t *prod, const int32_t *e,
-                                 const uint64_t *pt, uint64_t *ct, size_t count, hipStream_t s) {
-    const size_t words = count * 2 * c.k * (size_t)c.n;
-    if (words == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_encrypt_finish, dim3(grid_for(words)), dim3(256), 0, s, c, prod, e, pt, ct,
-                       count);
+template <class S, class D>
+static hipError_t convert(const S *src, D *dst, size_t count, hipStream_t s) {
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_convert<S, D>), dim3(grid_for(count)), dim3(256), 0, s, src, dst, count);
     return hipGetLastError();
+}
+hipError_t launch_widen_u32(const uint32_t *src, uint64_t *dst, size_t count, hipStream_t s) {
+    return convert(src, dst, count, s);
+}
+hipError_t launch_widen_i16(const int16_t *src, int32_t *dst, size_t count, hipStream_t s) {
+    return convert(src, dst, count, s);
+}
+hipError_t launch_narrow_u32(const uint64_t *src, uint32_t *dst, size_t count, hipStream_t s) {
+    return convert(src, dst, count, s);
 }
 
 hipError_t launch_bridge_combine(const DevCtx &c, const uint64_t *y, uint64_t *bits, uint64_t *eq,
