@@ -855,6 +855,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     if (f64) {
         f64 = false;
         for (int lg = 30; lg <= 50 && !f64; lg++) {
+            if ((double)lg * (double)ps.size() < need) continue;  // too small for so few primes: not searched
             std::vector<uint64_t> pf;
             if (aux_primes(1ull << lg, pf) && pf.size() <= ps.size()) {
                 ps.swap(pf);
@@ -898,8 +899,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
 
     // ---- device tables ----
     std::vector<PrimeConst> pc(c->K);
-    std::vector<Tw> tw((size_t)c->K * n), itw((size_t)c->K * n);
-    std::vector<TwF> twf(f64 ? 2 * (size_t)c->K * n : 0);  // forward, then inverse
+    std::vector<Tw> tw((size_t)c->K * n);  // the other twiddles: launch_twiddles
     // w centred modulo q with its quotient by q (one correction step of v qinv)
     auto centred = [](uint64_t w, uint64_t q, double qinv) {
         const double v = w > q / 2 ? -(double)(int64_t)(q - w) : (double)(int64_t)w;
@@ -934,23 +934,11 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
             P.m64f = wm.w;
             P.m64f_i = wm.wi;
         }
-        const uint64_t psi = find_psi(q, n), ipsi = hinv(psi, q);
-        std::vector<uint64_t> pw(n), ipw(n);
-        pw[0] = 1;
-        ipw[0] = 1;
-        const uint64_t psi_p = shoup(psi, q), ipsi_p = shoup(ipsi, q);
-        for (uint32_t i = 1; i < n; i++) {
-            pw[i] = mul_shoup(pw[i - 1], psi, psi_p, q);
-            ipw[i] = mul_shoup(ipw[i - 1], ipsi, ipsi_p, q);
-        }
+        const uint64_t psi = find_psi(q, n), psi_p = shoup(psi, q);
+        uint64_t w = 1;
         for (uint32_t i = 0; i < n; i++) {
-            const uint32_t r = bitrev(i, c->L);
-            tw[(size_t)l * n + i] = Tw{pw[r], shoup(pw[r], q)};
-            itw[(size_t)l * n + i] = Tw{ipw[r], shoup(ipw[r], q)};
-            if (f64) {
-                twf[(size_t)l * n + i] = centred(pw[r], q, qinv);
-                twf[((size_t)c->K + l) * n + i] = centred(ipw[r], q, qinv);
-            }
+            tw[(size_t)l * n + bitrev(i, c->L)] = Tw{w, shoup(w, q)};
+            w = mul_shoup(w, psi, psi_p, q);
         }
     }
 
@@ -1055,8 +1043,14 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     if (st == FHE_OK) st = scratch_address(hip_device, &c->scratch);
     if (st == FHE_OK) st = alloc_copy(&c->d_pc, pc.data(), pc.size() * sizeof(PrimeConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_tw, tw.data(), tw.size() * sizeof(Tw));
-    if (st == FHE_OK) st = alloc_copy(&c->d_itw, itw.data(), itw.size() * sizeof(Tw));
-    if (st == FHE_OK && f64) st = alloc_copy(&c->d_twf, twf.data(), twf.size() * sizeof(TwF));
+    const size_t tw_bytes = tw.size() * sizeof(Tw);
+    if (st == FHE_OK && (hipMalloc(&c->d_itw, tw_bytes) != hipSuccess ||
+                         (f64 && hipMalloc(&c->d_twf, 2 * tw.size() * sizeof(TwF)) != hipSuccess)))
+        st = FHE_ENOMEM;
+    if (st == FHE_OK && (launch_twiddles((const PrimeConst *)c->d_pc, (const Tw *)c->d_tw, (Tw *)c->d_itw,
+                                         (TwF *)c->d_twf, n, c->L, (int)c->K, nullptr) != hipSuccess ||
+                         hipStreamSynchronize(nullptr) != hipSuccess))
+        st = FHE_EDEVICE;
     if (st == FHE_OK) st = alloc_copy(&c->d_cc, cc, sizeof(ConvConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_mrc_q, mq, sizeof(MrcConst));
     if (st == FHE_OK) st = alloc_copy(&c->d_mrc_p, mp, sizeof(MrcConst));

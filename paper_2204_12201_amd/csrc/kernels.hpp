@@ -197,6 +197,9 @@ hipError_t launch_bridge_combine(const DevCtx &c, const uint64_t *y, uint64_t *b
 // out = sum_b 2^b bits[b] by Horner; signed_top: the leading bit weighs -2^(nbits-1)
 hipError_t launch_horner(const DevCtx &c, const uint64_t *bits, int nbits, uint64_t *out,
                          size_t count, int signed_top, hipStream_t s);
+// itw (and twf, forward then inverse, unless null) of all K primes from tw
+hipError_t launch_twiddles(const PrimeConst *pc, const Tw *tw, Tw *itw, TwF *twf, uint32_t n, int L, int K,
+                           hipStream_t s);
 // dst := src, 32-bit words; src may be pinned host memory (a copy of a few KiB
 // between kernels of one stream: the copy engine costs about 15 us of hand-over)
 hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s);

@@ -13,6 +13,7 @@
 #include "conv_mx.hpp"
 #include "kernels.hpp"
 #include "modarith.hpp"
+#include "ntt_core.hpp"
 
 namespace {
 
@@ -506,6 +507,36 @@ __global__ __launch_bounds__(256) void k_copy_words(const uint32_t *__restrict__
     for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
+// Grid (n/256 rounded up, K): the inverse and the floating-point twiddles from
+// the forward ones.  psi^n = -1, so psi^-r is q - w for w = psi^(n-r), and its
+// companion floor((q - w) 2^64 / q) is 2^64 - 1 less w's (w 2^64 / q is no
+// integer).  On the host these tables took longer than the forward one and
+// three more copies: a context at n = 8192, k = 5, 2.24 ms then and 0.86 so.
+__global__ __launch_bounds__(256) void k_twiddles(const PrimeConst *__restrict__ pc, const Tw *__restrict__ tw,
+                                                 Tw *__restrict__ itw, TwF *__restrict__ twf, uint32_t n, int L) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const size_t row = (size_t)blockIdx.y * n;
+    const PrimeConst &P = pc[blockIdx.y];
+    const Tw f = tw[row + i];
+    Tw g = f;
+    if (i) {
+        const uint32_t r = __brev(i) >> (32 - L), j = __brev(n - r) >> (32 - L);
+        const Tw m = tw[row + j];
+        g = Tw{P.q - m.w, ~m.wp};
+    }
+    itw[row + i] = g;
+    if (!twf) return;
+    // w centred modulo q with its quotient by q (one correction step of v qinv)
+    auto centred = [&](uint64_t w) {
+        const double v = w > P.q / 2 ? -(double)(int64_t)(P.q - w) : (double)(int64_t)w;
+        const double e = v * P.pinvf;
+        return TwF{v, __fma_rn(__fma_rn(-e, P.pf, v), P.pinvf, e)};
+    };
+    twf[row + i] = centred(f.w);
+    twf[(size_t)gridDim.y * n + row + i] = centred(g.w);
+}
+
 __global__ void k_validate(DevCtx c, const uint64_t *__restrict__ a, size_t words, int kmod, int off,
                            unsigned int *flag) {
     const size_t n = c.n;
@@ -973,6 +1004,12 @@ hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream
     if (words == 0) return hipSuccess;
     hipLaunchKernelGGL(k_copy_words, dim3(grid_for(words)), dim3(256), 0, s, (const uint32_t *)src, (uint32_t *)dst,
                        words);
+    return hipGetLastError();
+}
+
+hipError_t launch_twiddles(const PrimeConst *pc, const Tw *tw, Tw *itw, TwF *twf, uint32_t n, int L, int K,
+                           hipStream_t s) {
+    hipLaunchKernelGGL(k_twiddles, dim3((n + 255) / 256, K), dim3(256), 0, s, pc, tw, itw, twf, n, L);
     return hipGetLastError();
 }
 
