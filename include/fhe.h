@@ -134,9 +134,11 @@ size_t fhe_workspace_bytes(const fhe_ctx *ctx, int op, size_t count);
 fhe_status fhe_set_batch_limit(fhe_ctx *ctx, size_t max_items);
 
 /* Launch-shape switch of the product pipeline: chunks of at least min_rows
- * (item, limb) workgroups take the fused transform kernel, smaller ones the
- * unfused kernels (square != 0: the squaring path, whose default is 0 =
- * always fused; products default to 128).  Same words either way. */
+ * (item, limb) workgroups take the fused one-row-per-workgroup kernels, smaller
+ * ones the split transforms (where they do not apply, products take the unfused
+ * kernels; square != 0: the squaring path).  Until it is called the library
+ * chooses by ring size and by how full the last round of workgroups would be.
+ * Same words either way. */
 fhe_status fhe_set_fused_threshold(fhe_ctx *ctx, int square, size_t min_rows);
 
 /* Where the base conversions of `multiply` (top of this file) run: the
