@@ -475,8 +475,8 @@ bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     // rings without split transforms: measured at n = 16384, one product was
     // faster unfused (seven times as many workgroups), sixteen fused
     if (!c->split) return square || rows >= 128;
-    // floating-point fields have no fused kernels, and are faster at every size
-    // (n = 8192, 341 items: 1790 against 2562 us fused in integers; n = 4096,
+    // the fused kernels are integer ones: the floating-point field's split kernels
+    // are faster at every size (n = 8192, 341 items: 1790 against 2562 us fused in integers; n = 4096,
     // 512: 829 against 1011)
     if (c->dev.f64) return false;
     // without the matrix-core conversions the columns are not fused with them
