@@ -12,7 +12,9 @@
 // Field types:
 //  FieldU<LZ>  64-bit integers, the lazy butterflies of ntt_core.hpp.
 //  FieldF<BIG> signed integers held in doubles, for primes below 2^50.  A
-//              product y w mod p is computed exactly as
+//              product y w mod p is computed exactly (the floating-point modular
+//              product with fused multiply-add of van der Hoeven, Lecerf and
+//              Quintin, "Modular SIMD arithmetic in Mathemagix", 2016) as
 //                g = rint(y w/p), h = y w, l = fma(y, w, -h), (h - g p) + l,
 //              where h + l = y w exactly, h - g p is an integer below 2^53 (one
 //              fma, exact) and |y w - g p| <= p (1/2 + |y| 2^-53) for |w| <= p/2:
@@ -22,11 +24,14 @@
 //
 // Bounds of FieldF in units of p (LIM = 2^53 / p >= 8 is the most a value may
 // reach): a forward level takes the bound b to b + 1/2 + b/LIM.  Primes below
-// 2^47 (LIM >= 64) run the 14 levels from a canonical input without any
-// reduction.  Larger ones (BIG, LIM >= 8) go 1 -> 4.0 over pass 0, are
-// reduced to 1/2 on entry of the block part and again before its third pass
-// (1/2 -> 7.6 in eight levels).  An inverse level doubles sums and brings
-// differences to 1/2 + b/LIM: inv_pass_f states where sums are reduced.
+// 2^47 (LIM >= 64) run the levels from a canonical input without any reduction,
+// to 7.8, 8.4 and 9.1 for 12, 13 and 14 of them, and multiply these values as they
+// are: a product of two of them is at most 1/2 + 3 b^2/LIM (mulvar_f), 3.4, 3.9
+// and 4.4.  Larger ones (BIG, LIM >= 8) go 1 -> 4.1 over pass 0, are
+// reduced to 1/2 on entry of the block part, again before its third pass
+// (1/2 -> 7.6 in eight levels) and before a product (0.6).  An inverse level
+// doubles sums and brings differences to 1/2 + b/LIM: before_last and pass_end
+// state where sums are reduced.
 #pragma once
 #include "kernels.hpp"
 #include "modarith.hpp"
@@ -41,7 +46,8 @@ __device__ __forceinline__ double mulmod_f(double y, double w, double wi, double
     return __builtin_fma(-g, p, h) + l;
 }
 
-// a b mod p for two variables: |result| <= p (1/2 + |a b / p| 2^-51).
+// a b mod p for two variables: |result| <= p/2 + 3 |a b| 2^-53 (the roundings of
+// a b, 1/p and their product), and a b - g p exactly while that is below 2^52.
 __device__ __forceinline__ double mulvar_f(double a, double b, double p, double pinv) {
     const double h = a * b;
     const double g = __builtin_rint(h * pinv);
@@ -49,7 +55,7 @@ __device__ __forceinline__ double mulvar_f(double a, double b, double p, double 
     return __builtin_fma(-g, p, h) + l;
 }
 
-// x - rint(x / p) p: |result| <= p/2 + 1 for |x| <= 2^53.
+// x - rint(x / p) p: |result| <= p/2 + 2 for |x| <= 2^53.
 __device__ __forceinline__ double red_f(double x, double p, double pinv) {
     return __builtin_fma(-__builtin_rint(x * pinv), p, x);
 }
@@ -329,9 +335,11 @@ struct FieldF {
     // p): after three levels the slots whose low three bits are 0 or 1 hold up
     // to 8 or 4 p and are reduced before the last level (every sum and
     // difference then stays below 8p, every product below 1.02 p), the sums
-    // (slots 0..7) at the end.  Otherwise (LIM >= 64, inputs at most 2p): slots
-    // 0..3 (at most 32p) at the end.  Shorter passes (inputs at most 1.02 p): the
-    // sums at the end.
+    // (slots 0..7) at the end.  Otherwise (LIM >= 64): slots 0..3 at the end, which
+    // leaves the others below 2p; inputs are at most 3.4 p in the first pass of
+    // n = 4096 (unreduced products: slot 0 reaches 55p) and 2p in the others (32p).
+    // Shorter passes, the first of n = 8192 and 16384 (inputs at most 4.4 p, BIG 0.6
+    // p): the sums, at most 18p (BIG 2.4 p), at the end, products stay below 0.8 p.
     template <int NR>
     __device__ __forceinline__ void before_last(V (&x)[NR][16]) const {
         if constexpr (BIG) {
