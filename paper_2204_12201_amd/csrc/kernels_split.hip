@@ -638,6 +638,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         for (int i = w; i < k; i += W, cnt++)
             digit_block<L, Fd>(f, D + ((item * k + i) * k + j) * (size_t)n, rlk + (((size_t)i * 2 + 0) * k + j) * n,
                                rlk + (((size_t)i * 2 + 1) * k + j) * n, acc, cnt, lds, lane, tid, tw);
+        f.acc_part(acc, k);
 #pragma unroll
         for (int s = 0; s < 16; s++) {
             lds_add(&sums[s * 64 + lane], acc[0][s]);

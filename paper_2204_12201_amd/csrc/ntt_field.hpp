@@ -276,6 +276,7 @@ struct FieldU {
     template <int NR>
     __device__ __forceinline__ void key_operands(V (&)[NR][16]) const {}
     __device__ __forceinline__ void acc_mid(V (&)[2][16], int) const {}
+    __device__ __forceinline__ void acc_part(V (&)[2][16], int) const {}
     __device__ __forceinline__ V key(uint64_t w) const { return w; }
     __device__ __forceinline__ V acc(V a, V x, V key) const { return a + mont_mul_lazy_u(x, key, q, qi); }
     __device__ __forceinline__ V acc_out(V a) const { return csub(csub(csub(a, q << 4), q << 3), q << 2); }
@@ -385,10 +386,18 @@ struct FieldF {
     __device__ __forceinline__ V add2(V a, V b) const { return red_f(a + b, p, pinv); }
     template <int NR>
     __device__ __forceinline__ void key_operands(V (&x)[NR][16]) const { reduce_all(x); }
-    // before product number cnt of the sum: at most eight products below 0.9 p
-    // between reductions where 8p is the limit
+    // Key sums.  BIG (operands reduced to p/2, keys below p): a product is at most
+    // p (1/2 + 3/16), 3/(2 LIM) for the quotient's three roundings (mulvar_f);
+    // eight of them, or eight and a reduced sum, stay below 8p.  Otherwise the
+    // forward values reach 9.1p and a product 0.93p: 16 of them stay below 64p.
+    // acc_mid: before product number cnt of one wave's sum.
     __device__ __forceinline__ void acc_mid(V (&a)[2][16], int cnt) const {
         if ((cnt & 7) == 7) reduce_all(a);
+    }
+    // before the sums of up to eight waves meet, of k products in all: more than
+    // eight products could pass 8p, eight reduced sums stay near 4p
+    __device__ __forceinline__ void acc_part(V (&a)[2][16], int k) const {
+        if (k > 8) reduce_all(a);
     }
     __device__ __forceinline__ V key(uint64_t w) const { return u52_to_f(w); }
     __device__ __forceinline__ V acc(V a, V x, V key) const { return a + mulvar_f(x, key, p, pinv); }

@@ -1,5 +1,5 @@
 // Host build of the floating-point field of the split transforms
-// (csrc/ntt_field.hpp): its own passes, reductions and products, run
+// (csrc/ntt_field.hpp): its own passes, reductions, products and key sums, run
 // thread by thread on the CPU, against the same transforms modulo p in integers.
 // Values are congruent representatives pushed to the ends of the ranges that the
 // header states, so that a sum leaving the doubles' 53 bits changes a residue.
@@ -211,6 +211,34 @@ struct Check {
             }
         }
     }
+
+    // The key sums of k digits: few items (waves w, w + W, ... meet in one sum) and
+    // many (one wave takes all), every product at `prod` (units of p).
+    void keys(double prod) const {
+        const F f(c, 0);
+        for (int k = 1; k <= 16; k++)
+            for (int sign = -1; sign <= 1; sign += 2)
+                for (int few = 0; few < 2; few++) {
+                    const int W = !few ? 1 : k < 8 ? (k < 2 ? 2 : k) : 8;
+                    const double v = sign * (2.0 * std::floor(prod * (double)p / 2) - 1);  // odd
+                    double sum = 0.0;
+                    for (int wave = 0; wave < W; wave++) {
+                        double acc[2][16] = {};
+                        int cnt = 0;
+                        for (int i = wave; i < k; i += W, cnt++) {
+                            f.acc_mid(acc, cnt);
+                            for (auto &row : acc)
+                                for (double &a : row) a += v;
+                        }
+                        if (few) f.acc_part(acc, k);
+                        sum += acc[1][7];
+                        expect(std::fabs(sum) < LIMIT, "key sum bound", k, p, W);
+                    }
+                    const double out = f.acc_out(sum);
+                    expect(residue(out, p) == residue(v, p) * (u128)k % p, "key sum", k, p, W);
+                    expect(std::fabs(out) <= (double)p / 2 + 2.0, "reduced key sum", k, p, W);
+                }
+    }
 };
 
 // The bounds of the header in units of p: LIM = 2^53 / p.
@@ -222,6 +250,7 @@ static void check(uint64_t p) {
     for (int l = 0; l < L; l++) b += 0.5 + b / lim;
     if (BIG) b = 0.5;
     t.tensor(b, 0.5 + 3.0 * b * b / lim);  // b^2 p and three roundings of the quotient
+    t.keys(0.5 + 3.0 * b / lim);           // b p and the same
 }
 
 int main(int argc, char **argv) {

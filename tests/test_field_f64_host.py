@@ -1,8 +1,8 @@
 """The floating-point field of the split transforms (csrc/ntt_field.hpp) built for
-the host and run on the CPU: its own passes, reductions, products
-(of unreduced operands where the field takes them), against the same transforms in
-integers, with congruent values pushed to the ends of the ranges that the header
-derives (host_field_f64.cpp)."""
+the host and run on the CPU: its own passes, reductions, products (of unreduced
+operands where the field takes them) and key sums of 1 to 16 digits, against the
+same transforms in integers, with congruent values pushed to the ends of the ranges
+that the header derives (host_field_f64.cpp)."""
 import os
 import shutil
 import subprocess
