@@ -449,21 +449,21 @@ __global__ void k_horner(DevCtx c, const uint64_t *__restrict__ bits, int nbits,
 }
 
 // One step of the comparisons of a group of pairs (fhe_less_than's circuit,
-// bits i = 0 .. nbits of every pair's items at once): row blockIdx.y = q count +
-// j is item j of pair q, whose bit vectors are P.a[q], P.b[q] [count][nbits]; Pr
-// [pairs][count][nbits] holds the products a_i b_i and T the last product
+// bits i = 0 .. nbits of every pair's items at once): row y0 + blockIdx.y =
+// q count + j is item j of pair q, whose bit vectors are P.a[q], P.b[q]
+// [count][nbits]; Pr [pairs][count][nbits] holds the products a_i b_i and T the last product
 // e (lt - d).  With d_i = b_i - a_i b_i and lt = d_0 or T + d_(i-1):
 // i < nbits: E = e_i = 1 - ((a_i + b_i) - 2 a_i b_i), T = lt - d_i;
-// i == nbits: the result to lt.  grid (2 k n / 256, pairs count).  Bound by its
-// seven streams; the steps it replaces were seven launches a bit.
-__global__ __launch_bounds__(256) void k_lt_step(DevCtx c, LtPairs P, int count, int nbits, int i,
+// i == nbits: the result to lt.  grid (2 k n / 256, rows of the launch from y0).
+// Bound by its seven streams; the steps it replaces were seven launches a bit.
+__global__ __launch_bounds__(256) void k_lt_step(DevCtx c, LtPairs P, int count, int nbits, int i, int y0,
                                                  const uint64_t *__restrict__ Pr, uint64_t *__restrict__ E,
                                                  uint64_t *__restrict__ T, uint64_t *__restrict__ lt) {
     const uint32_t W = 2u * c.k * c.n, p = blockIdx.x * 256 + threadIdx.x;
     if (p >= W) return;
     const int limb = (int)((p >> c.L) % (uint32_t)c.k);
     const uint64_t q = c.pc[limb].q;
-    const int y = (int)blockIdx.y, pair = y / count, j = y % count;
+    const int y = y0 + (int)blockIdx.y, pair = y / count, j = y % count;
     const uint64_t *a = P.a[pair] + (size_t)j * nbits * W + p, *b = P.b[pair] + (size_t)j * nbits * W + p;
     const uint64_t *pr = Pr + (size_t)y * nbits * W + p;
     const size_t o = (size_t)y * W + p;
@@ -487,14 +487,14 @@ __global__ __launch_bounds__(256) void k_lt_step(DevCtx c, LtPairs P, int count,
 // the others in ascending order; against o < cl the factor is lt of the pair
 // (o, cl), against o > cl it is 1 - lt of (cl, o).  lt [pairs][count], pairs
 // ordered by first class, then second; out [ncls][count].  grid (2 k n / 256,
-// ncls count).
+// rows of the launch from y0).
 __global__ __launch_bounds__(256) void k_argmax_factor(DevCtx c, const uint64_t *__restrict__ lt, int ncls, int count,
-                                                       int t, uint64_t *__restrict__ out) {
+                                                       int t, int y0, uint64_t *__restrict__ out) {
     const uint32_t W = 2u * c.k * c.n, p = blockIdx.x * 256 + threadIdx.x;
     if (p >= W) return;
     const int limb = (int)((p >> c.L) % (uint32_t)c.k);
     const uint64_t q = c.pc[limb].q;
-    const int y = (int)blockIdx.y, cl = y / count, j = y % count, o = t <= cl ? t - 1 : t;
+    const int y = y0 + (int)blockIdx.y, cl = y / count, j = y % count, o = t <= cl ? t - 1 : t;
     const int lo = o < cl ? o : cl, hi = o < cl ? cl : o;
     const size_t pair = (size_t)lo * (2 * ncls - lo - 1) / 2 + (hi - lo - 1);
     const uint64_t v = lt[(pair * count + j) * W + p];
@@ -1013,20 +1013,31 @@ hipError_t launch_twiddles(const PrimeConst *pc, const Tw *tw, Tw *itw, TwF *twf
     return hipGetLastError();
 }
 
+// launch(y0, rows) over `rows` rows of ciphertexts: a grid holds 65535 of them.
+template <class Launch>
+static hipError_t row_launches(size_t rows, const Launch &launch) {
+    hipError_t e = hipSuccess;
+    for (size_t y = 0; y < rows && e == hipSuccess; y += 65535) {
+        launch((int)y, (unsigned)(rows - y < 65535 ? rows - y : 65535));
+        e = hipGetLastError();
+    }
+    return e;
+}
+static unsigned row_blocks(const DevCtx &c) { return (2u * (unsigned)c.k * (unsigned)c.n + 255) / 256; }
+
 hipError_t launch_lt_step(const DevCtx &c, const LtPairs &P, int pairs, int count, int nbits, int i,
                           const uint64_t *Pr, uint64_t *E, uint64_t *T, uint64_t *lt, hipStream_t s) {
-    const unsigned W = 2u * (unsigned)c.k * (unsigned)c.n;
-    hipLaunchKernelGGL(k_lt_step, dim3((W + 255) / 256, (unsigned)(pairs * count)), dim3(256), 0, s, c, P, count, nbits,
-                       i, Pr, E, T, lt);
-    return hipGetLastError();
+    return row_launches((size_t)pairs * count, [&](int y0, unsigned rows) {
+        hipLaunchKernelGGL(k_lt_step, dim3(row_blocks(c), rows), dim3(256), 0, s, c, P, count, nbits, i, y0, Pr, E, T,
+                           lt);
+    });
 }
 
 hipError_t launch_argmax_factor(const DevCtx &c, const uint64_t *lt, int ncls, int count, int t, uint64_t *out,
                                 hipStream_t s) {
-    const unsigned W = 2u * (unsigned)c.k * (unsigned)c.n;
-    hipLaunchKernelGGL(k_argmax_factor, dim3((W + 255) / 256, (unsigned)(ncls * count)), dim3(256), 0, s, c, lt, ncls,
-                       count, t, out);
-    return hipGetLastError();
+    return row_launches((size_t)ncls * count, [&](int y0, unsigned rows) {
+        hipLaunchKernelGGL(k_argmax_factor, dim3(row_blocks(c), rows), dim3(256), 0, s, c, lt, ncls, count, t, y0, out);
+    });
 }
 
 hipError_t launch_validate(const DevCtx &c, const uint64_t *a, size_t nrows, int kmod, int off,
