@@ -1159,11 +1159,17 @@ static size_t lt_group_bytes(const fhe_ctx *c, size_t pairs, size_t count, size_
            fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, items);
 }
 
-// Bits per item that the workspace sizes make room for: batches of up to 64
-// products of n = 16384 (about four times what the chip's CUs hold of one
-// product's blocks), at least the 2 and at most the 8 of a comparison.
+// Whether `items` bit products go in one batch: up to 128 of n = 16384.  Measured
+// there side by side and one bit after the other: 25 comparisons of 5 bits 6014
+// and 7499 us, 64 of 2 bits 4661 and 5349; the workspace grows with the batch.
+static bool lt_small(const fhe_ctx *c, size_t items) { return items * c->n <= ((size_t)128 << 14); }
+
+// Bits per item that the workspace sizes make room for: batches of about 64
+// products of n = 16384, at least the 2 and at most the 8 of a comparison; none
+// where lt_small does not even allow 2.
 static size_t lt_bits_room(const fhe_ctx *c, size_t rows) {
     const size_t batch = ((size_t)64 << 14) / c->n, most = rows ? (batch + rows - 1) / rows : 2;
+    if (!lt_small(c, 2 * rows)) return 0;
     return most < 2 ? 2 : most > 8 ? 8 : most;
 }
 
@@ -1202,14 +1208,21 @@ size_t fhe_workspace_bytes(const fhe_ctx *c, int op, size_t count) {
         case FHE_OP_COMPARE: {
             // one bit at a time, or room for the bits of a comparison side by side
             // (lt_group_bytes; the call takes what fits)
-            const size_t a = compare_seq_bytes(c, count), b = lt_group_bytes(c, 1, count, lt_bits_room(c, count));
+            const size_t a = compare_seq_bytes(c, count), bits = lt_bits_room(c, count);
+            const size_t b = bits ? lt_group_bytes(c, 1, count, bits) : 0;
             return a > b ? a : b;
         }
         case FHE_OP_ARGMAX: {
-            // one comparison at a time, or room for the bits of three pairs side
+            // one comparison at a time, or, where that many share a batch, room
+            // for the bits of three pairs (two, one with all the bits that do) side
             // by side, with the results of six pairs and a factor per class
-            const size_t a = argmax_seq_bytes(c, count);
-            const size_t b = 10 * count * ct_words(c) * 8 + lt_group_bytes(c, 3, count, lt_bits_room(c, 3 * count));
+            const size_t a = argmax_seq_bytes(c, count), ctb = count * ct_words(c) * 8;
+            size_t pairs = 3, bits = 0;
+            while (pairs && !(bits = lt_bits_room(c, pairs * count))) pairs--;
+            if (!pairs) return a;
+            if (pairs == 1)
+                while (bits < 8 && lt_small(c, (bits + 1) * count)) bits++;
+            const size_t b = 10 * ctb + lt_group_bytes(c, pairs, count, bits);
             return a > b ? a : b;
         }
         case FHE_OP_BRIDGE_POWERS: {
@@ -2152,10 +2165,6 @@ static fhe_status lt_group(fhe_ctx *c, const uint64_t *rlk, const LtPairs &P, si
     return FHE_OK;
 }
 
-// Whether one more than `count` items' products still share the chip: beyond
-// about 64 products of n = 16384 a batch gains nothing from being larger.
-static bool lt_small(const fhe_ctx *c, size_t items) { return items * c->n <= ((size_t)128 << 14); }
-
 fhe_status fhe_less_than(fhe_ctx *c, const uint64_t *rlk, const uint64_t *a, const uint64_t *b, uint32_t nbits,
                          uint64_t *out, size_t count, void *ws, size_t ws_bytes, hipStream_t st) {
     if (!c) return FHE_EINVAL;
@@ -2189,7 +2198,7 @@ fhe_status fhe_argmax(fhe_ctx *c, const uint64_t *rlk, const uint64_t *scores, u
     if (ws_bytes < argmax_seq_bytes(c, count)) return FHE_EWORKSPACE;  // enough for one comparison at a time
     FHE_TRY(check_canonical(c, scores, ncls * count * nbits * 2 * c->k, c->k, 0, st));
     // Groups of pairs side by side where the batches stay small enough to gain
-    // and the workspace holds them (fhe_workspace_bytes makes room for three pairs)
+    // and the workspace holds them (fhe_workspace_bytes makes room for up to three pairs)
     const size_t np = (size_t)ncls * (ncls - 1) / 2;
     if (nbits > 1 && lt_small(c, count * nbits)) {
         const size_t fixed = (np + ncls) * cw * 8;
@@ -2197,8 +2206,11 @@ fhe_status fhe_argmax(fhe_ctx *c, const uint64_t *rlk, const uint64_t *scores, u
         while (per > 0 && (fixed + lt_group_bytes(c, per, count, nbits) > ws_bytes ||
                            (per > 1 && !lt_small(c, per * count * nbits))))
             per--;
-        // the factors' products share the groups' product workspace
-        if (per > 0 && fixed + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, ncls * count) <= ws_bytes) {
+        // the factors' products share the groups' product workspace, as many
+        // classes at a time as it holds
+        size_t mcls = ncls;
+        while (mcls > 1 && fixed + fhe_workspace_bytes(c, FHE_OP_MUL_RELIN, mcls * count) > ws_bytes) mcls--;
+        if (per > 0) {
             uint64_t *lt = (uint64_t *)ws, *Y = lt + np * cw;
             void *gws = Y + ncls * cw;
             LtPairs P{};
@@ -2217,7 +2229,10 @@ fhe_status fhe_argmax(fhe_ctx *c, const uint64_t *rlk, const uint64_t *scores, u
                 uint64_t *dst = t == 1 ? out : Y;
                 FHE_TRY(run(c, KK_ELEMENTWISE, st,
                             [&] { return launch_argmax_factor(c->dev, lt, (int)ncls, (int)count, (int)t, dst, st); }));
-                if (t > 1) FHE_TRY(mul_relin_impl(c, rlk, out, Y, out, ncls * count, gws, st));
+                for (size_t a = 0; t > 1 && a < ncls; a += mcls) {
+                    const size_t m = std::min(mcls, ncls - a);
+                    FHE_TRY(mul_relin_impl(c, rlk, out + a * cw, Y + a * cw, out + a * cw, m * count, gws, st));
+                }
             }
             return FHE_OK;
         }

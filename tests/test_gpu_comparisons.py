@@ -1,6 +1,7 @@
 """Comparisons and argmax of many rows of small rings: more rows than a grid holds
 (65535), with the bits of all items side by side, give the words of the same calls
-in turn or in parts, and of the oracle."""
+in turn or in parts, and of the oracle; the workspace sizes ask for more than one
+comparison at a time needs only where the call uses it."""
 import ctypes
 
 import numpy as np
@@ -101,3 +102,60 @@ def test_more_comparison_rows_than_a_grid():
     for j in (0, 65534, 65535):
         want = bfv.less_than(s.P, s.rlk, list(ab[0, j]), list(ab[1, j]))
         assert (fhe.to_numpy_u64(got[j]) == want).all(), j
+
+
+@pytest.mark.parametrize("n,bits", [(256, (40,)), (256, (40,) * 3), (4096, (36,) * 3)])
+def test_room_only_where_it_is_used(n, bits):
+    """Argmax of three classes of two bits, items on both sides of every step of the
+    size: side by side in the default workspace where that is larger than one
+    comparison at a time needs, and the sequential size elsewhere."""
+    s = Setup(n, bfv.ntt_primes(n, bits[0], len(bits)))
+    most = (128 << 14) // n  # bit products that share a batch
+    print(f"[gpu-comparisons] sizes n={n} k={s.k}", flush=True)
+    for count in (1, 3, most // 6, most // 6 + 1, most // 4, most // 4 + 1, most // 2, most // 2 + 1, most):
+        seq = 8 * count * s.ctb + s.bytes(fhe.OP_MUL_RELIN, count)
+        need = s.bytes(fhe.OP_ARGMAX, count)
+        side = 2 * count <= most
+        assert (need > seq) == side, (count, need, seq)
+        assert s.bytes(fhe.OP_COMPARE, count) >= seq - 2 * count * s.ctb
+        if not side:
+            assert s.bytes(fhe.OP_COMPARE, count) == seq - 2 * count * s.ctb
+        if need > 1 << 33:
+            continue
+        sc = fhe.from_numpy_u64(np.zeros((3, count, 2, 2, s.k, n), dtype=np.uint64), "cuda")
+        steps = s.argmax(sc, need)[1]
+        groups = -(-3 // min(3, max(1, most // (2 * count))))
+        assert steps == groups * 2 + 2 if side else steps > 8, (count, steps)
+        if side:  # four classes
+            sc = fhe.from_numpy_u64(np.zeros((4, count, 2, 2, s.k, n), dtype=np.uint64), "cuda")
+            assert s.argmax(sc, need)[1] < 24, count
+
+
+def test_factors_in_parts():
+    """Four classes where the workspace holds the factors' products of two at a time."""
+    import torch
+    n, ncls, count, nbits = 256, 4, 4000, 2
+    s = Setup(n, bfv.ntt_primes(n, 40, 3))
+    print(f"[gpu-comparisons] argmax n={n} ncls={ncls} count={count}", flush=True)
+    sc = inputs.uniform_ciphertexts(n, s.qs, ncls * count * nbits, 9).reshape(ncls, count, nbits, 2, s.k, n)
+    d = up(sc)
+    need = s.bytes(fhe.OP_ARGMAX, count)
+    assert need < 10 * count * s.ctb + s.bytes(fhe.OP_MUL_RELIN, 3 * count)
+    got, steps = s.argmax(d, need)
+    assert steps == 6 * nbits + 3
+    in_turn, _ = s.argmax(d, 8 * count * s.ctb + s.bytes(fhe.OP_MUL_RELIN, count))
+    assert torch.equal(got, in_turn)
+    want = bfv.argmax(s.P, s.rlk, [list(sc[c, 1]) for c in range(ncls)])
+    for c in range(ncls):
+        assert (fhe.to_numpy_u64(got[c, 1]) == want[c]).all(), c
+
+
+def test_sizes_of_many_items():
+    """At the largest ring: thousands of items need what one comparison at a time
+    needs (3000: 59 GB, where room for groups that never run would take 222)."""
+    s = Setup(16384, inputs.PRIMES[(16384, 55)])
+    for count in (65, 256, 1000, 3000):
+        mul = s.bytes(fhe.OP_MUL_RELIN, count)
+        assert s.bytes(fhe.OP_ARGMAX, count) == 8 * count * s.ctb + mul
+        assert s.bytes(fhe.OP_COMPARE, count) == 6 * count * s.ctb + mul
+    assert s.bytes(fhe.OP_ARGMAX, 32) < 4 << 30
