@@ -894,9 +894,10 @@ struct SplitL {
     }
     static hipError_t inv_scale(const DevCtx &c, const uint64_t *Dt, uint64_t *out, uint64_t *C2, uint64_t *D,
                                 size_t items, hipStream_t s) {
-        return tensor_field(c, [&](auto fam) {
+        hipError_t e = hipSuccess;  // of the launch, which digit_field takes from the runtime
+        const hipError_t rest = tensor_field(c, [&](auto fam) {
             typedef decltype(fam) F;
-            (void)digit_field(c, [&](auto dfam, auto raw) {
+            e = digit_field(c, [&](auto dfam, auto raw) {
                 typedef decltype(dfam) DF;
                 constexpr bool RAW = decltype(raw)::value;
                 if constexpr (std::is_same<F, FamF>::value == std::is_same<DF, FamF>::value) {
@@ -905,6 +906,7 @@ struct SplitL {
                 }
             });
         });
+        return e != hipSuccess ? e : rest;
     }
 };
 
