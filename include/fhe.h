@@ -136,9 +136,11 @@ fhe_status fhe_set_batch_limit(fhe_ctx *ctx, size_t max_items);
 /* Launch-shape switch of the product pipeline: chunks of at least min_rows
  * (item, limb) workgroups take the fused one-row-per-workgroup kernels, smaller
  * ones the split transforms (where they do not apply, products take the unfused
- * kernels; square != 0: the squaring path).  Until it is called the library
- * chooses by ring size and by how full the last round of workgroups would be.
- * Same words either way. */
+ * kernels; square != 0: the squaring path).  Until it is called, and after
+ * FHE_FUSED_AUTO, the library chooses by ring size and by how full the last
+ * round of workgroups would be (rings without split transforms: squarings always
+ * fused, products from 128 on).  Same words either way. */
+#define FHE_FUSED_AUTO ((size_t)-2)
 fhe_status fhe_set_fused_threshold(fhe_ctx *ctx, int square, size_t min_rows);
 
 /* Where the base conversions of `multiply` (top of this file) run: the
@@ -248,10 +250,11 @@ fhe_status fhe_mul_relin_static(fhe_ctx *ctx, const uint64_t *rlk_dev, const uin
  * chunk caps count, count/2, count/4 (never above the current cap) and with
  * the fused transform kernel or the unfused ones, three timed runs each after
  * a warm-up on `stream` (synchronous), and keeps the fastest: the chunk cap
- * (as fhe_set_batch_limit) and the fused/unfused threshold of that product
- * kind, set so that chunks of the chosen size take the chosen path.  Results
- * of every call are the same words whatever the choice; only speed changes.
- * *chunk and *fused (may be NULL) receive the choice.  out is overwritten.
+ * (as fhe_set_batch_limit) and the path of that product kind, so that chunks of
+ * the chosen size take the chosen one: a threshold, or under FHE_FUSED_AUTO on a
+ * ring with split transforms that chunk size alone, if the library would have
+ * chosen otherwise (other sizes keep its choice).  Results of every call are the
+ * same words whatever the choice; only speed changes.  *chunk and *fused (may be NULL) receive the choice.  out is overwritten.
  * ws: FHE_OP_MUL_RELIN (FHE_OP_SQUARE_RELIN when a == b) bytes for count. */
 fhe_status fhe_autotune_mul_relin(fhe_ctx *ctx, const uint64_t *rlk_dev, const uint64_t *a,
                                   const uint64_t *b, uint64_t *out, size_t count, void *ws,

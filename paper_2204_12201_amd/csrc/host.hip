@@ -293,7 +293,7 @@ struct EvPair {
 
 }  // namespace
 
-constexpr size_t kFusedAuto = SIZE_MAX - 1;
+constexpr size_t kFusedAuto = FHE_FUSED_AUTO;
 
 struct fhe_ctx {
     int device = 0;
@@ -310,9 +310,12 @@ struct fhe_ctx {
     size_t batch_limit = 0, default_limit = 0;
     // fused product kernel (k_mul_tensor / k_square_tensor) from this many
     // (item, limb) workgroups per launch on; fewer take the unfused kernels
-    // (index 0: products of two ciphertexts, 1: squarings).  kFusedAuto: the
-    // measured rule of fused_wanted
+    // (index 0: products of two ciphertexts, 1: squarings).  kFusedAuto (rings
+    // with split transforms): the measured rule of fused_wanted, but for chunks of
+    // tuned_rows, for which the autotuner measured the other choice to be faster
     size_t fused_min_rows[2] = {kFusedAuto, kFusedAuto};
+    size_t tuned_rows[2] = {0, 0};
+    bool tuned_fused[2] = {false, false};
     // launches of the split transforms (kernels_split.hip), null for other ring
     // degrees; key switching takes them where relin_split_ok says that its sums
     // stay in range and relin_is_split that they are faster
@@ -467,14 +470,17 @@ double fused_fill(const fhe_ctx *c, size_t rows) {
     return (double)rows / (double)((rows + round - 1) / round * round);
 }
 
+// The library's own choice as a threshold.  Rings without split transforms:
+// measured at n = 16384, one product was faster unfused (seven times as many
+// workgroups), sixteen fused; squarings are always fused.
+size_t auto_threshold(const fhe_ctx *c, bool square) { return c->split ? kFusedAuto : square ? 0 : 128; }
+
 // Whether the transform phase takes the fused kernel (one workgroup per row and
 // item) and not the split or, for rings without those, the unfused kernels.
 bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     const size_t rows = items * c->K, thr = c->fused_min_rows[square ? 1 : 0];
     if (thr != kFusedAuto) return rows >= thr;
-    // rings without split transforms: measured at n = 16384, one product was
-    // faster unfused (seven times as many workgroups), sixteen fused
-    if (!c->split) return square || rows >= 128;
+    if (rows == c->tuned_rows[square ? 1 : 0]) return c->tuned_fused[square ? 1 : 0];
     // the fused kernels are integer ones: the floating-point field's split kernels
     // are faster at every size (n = 8192, 341 items: 1790 against 2562 us fused in integers; n = 4096,
     // 512: 829 against 1011)
@@ -1118,6 +1124,7 @@ fhe_status fhe_ctx_create(const fhe_params *p, int hip_device, fhe_ctx **out) {
     // split transforms: the integer key switching sums operands below
     // 4 (L + 1) q by column products, whose high halves must not overflow
     c->split = split_ops((int)c->L);
+    for (int sq = 0; sq < 2; sq++) c->fused_min_rows[sq] = auto_threshold(c, sq);
     c->relin_split_ok = c->split && (f64 || (d.lazy_q && qmax < (1ull << 58)));
     // default chunk: about 8 GiB of product workspace
     size_t per = item_words_mul(c, false) * 8;
@@ -1247,7 +1254,8 @@ size_t fhe_workspace_bytes(const fhe_ctx *c, int op, size_t count) {
 
 fhe_status fhe_set_fused_threshold(fhe_ctx *c, int square, size_t min_rows) {
     if (!c) return FHE_EINVAL;
-    c->fused_min_rows[square ? 1 : 0] = min_rows;
+    c->fused_min_rows[square ? 1 : 0] = min_rows == kFusedAuto ? auto_threshold(c, square) : min_rows;
+    c->tuned_rows[square ? 1 : 0] = 0;
     drop_graphs(c);
     return FHE_OK;
 }
@@ -1623,11 +1631,22 @@ fhe_status fhe_autotune_mul_relin(fhe_ctx *c, const uint64_t *rlk, const uint64_
         c->fused_min_rows[square ? 1 : 0] = saved_thr;
         return st_all;
     }
-    // keep the winner: the chunk cap, and a threshold that sends this batch's
-    // chunks to the faster product path
+    // keep the winner: the chunk cap, and what sends this batch's chunks to the
+    // faster product path: a threshold, or where the library chooses by size (which
+    // chunks of other sizes keep) an exception where it would choose otherwise
     c->batch_limit = best_cap;
     const size_t rows = best_cap * c->K;
-    c->fused_min_rows[square ? 1 : 0] = best_fused ? (saved_thr < rows ? saved_thr : rows) : rows + 1;
+    const int sq = square ? 1 : 0;
+    if (saved_thr == kFusedAuto) {
+        c->fused_min_rows[sq] = kFusedAuto;
+        c->tuned_rows[sq] = 0;
+        if (fused_wanted(c, square, best_cap) != (best_fused != 0)) {
+            c->tuned_rows[sq] = rows;
+            c->tuned_fused[sq] = best_fused != 0;
+        }
+    } else {
+        c->fused_min_rows[sq] = best_fused ? (saved_thr < rows ? saved_thr : rows) : rows + 1;
+    }
     if (chunk_out) *chunk_out = best_cap;
     if (fused_out) *fused_out = best_fused;
     return FHE_OK;

@@ -19,6 +19,7 @@ LIBPATH = os.path.join(HERE, "libfhe.so")
 ENC_SLOTS, ENC_COEFF = 0, 1
 OP_MUL_RELIN, OP_SQUARE_RELIN, OP_BRIDGE, OP_KEYGEN, OP_ENCRYPT, OP_DECRYPT, OP_RLK_IMPORT = range(1, 8)
 OP_WEIGHTED_SUM, OP_GATE, OP_COMPARE, OP_ARGMAX, OP_MOD_TO_INT, OP_BRIDGE_POWERS = range(8, 14)
+FUSED_AUTO = 2 ** 64 - 2  # fhe_set_fused_threshold: the library chooses
 GATES = {"AND": 0, "NAND": 1, "OR": 2, "NOR": 3, "XOR": 4, "XNOR": 5, "NOT": 6, "MUX": 7}
 
 STATUS = {0: "ok", -1: "invalid argument", -2: "parameter set rejected", -3: "device allocation failed",
@@ -329,6 +330,7 @@ class Context:
         return lib().fhe_conv_method(self._h) == 1
 
     def set_fused_threshold(self, square: bool, min_rows: int):
+        """fhe_set_fused_threshold; FUSED_AUTO: the library chooses."""
         _check(lib().fhe_set_fused_threshold(self._h, 1 if square else 0, min_rows), "fhe_set_fused_threshold")
 
     def square_chain(self, rlk, x, depth: int, graph: bool = False):
