@@ -1199,10 +1199,9 @@ size_t fhe_workspace_bytes(const fhe_ctx *c, int op, size_t count) {
         case FHE_OP_KEYGEN:
             return (6 * k * n) * 8 + n + 4 * n + k * n * 8 + 4 * n + 64;
         case FHE_OP_ENCRYPT:
-            return (2 * k * n + count * k * n + count * 2 * k * n + count * n) * 8 + count * n +
-                   count * 2 * n * 4 + 256;
+            return (2 * k * n + count * k * n + count * n) * 8 + count * n + count * 2 * n * 4 + 256;
         case FHE_OP_DECRYPT:
-            return (k * n + 2 * count * k * n + count * n) * 8 + n + 256;
+            return (k * n + count * k * n + count * n) * 8 + n + 256;
         case FHE_OP_RLK_IMPORT:
             return 0;
         case FHE_OP_WEIGHTED_SUM:
@@ -1382,7 +1381,7 @@ fhe_status fhe_encrypt(fhe_ctx *c, const uint64_t *pk_dev, const uint64_t *pt, c
     if (!pk_dev || !pt || !u || !e || !ct_dev || !ws) return FHE_EINVAL;
     if (ws_bytes < fhe_workspace_bytes(c, FHE_OP_ENCRYPT, count)) return FHE_EWORKSPACE;
     const size_t n = c->n, k = c->k, kn = k * n, words = count * n;
-    uint64_t *PK = (uint64_t *)ws, *U = PK + 2 * kn, *prod = U + count * kn, *pt_dev = prod + 2 * count * kn;
+    uint64_t *PK = (uint64_t *)ws, *U = PK + 2 * kn, *pt_dev = U + count * kn;
     int8_t *u_dev = (int8_t *)(pt_dev + count * n);
     int32_t *e_dev = (int32_t *)(u_dev + ((count * n + 63) & ~(size_t)63));
     const DevCtx &d = c->dev;
@@ -1447,7 +1446,7 @@ fhe_status fhe_decrypt(fhe_ctx *c, const int8_t *s, const uint64_t *ct_dev, uint
     if (!s || !ct_dev || !pt || !ws) return FHE_EINVAL;
     if (ws_bytes < fhe_workspace_bytes(c, FHE_OP_DECRYPT, count)) return FHE_EWORKSPACE;
     const size_t n = c->n, k = c->k, kn = k * n;
-    uint64_t *S = (uint64_t *)ws, *C1 = S + kn, *X = C1 + count * kn, *pt_dev = X + count * kn;
+    uint64_t *S = (uint64_t *)ws, *X = S + kn, *pt_dev = X + count * kn;
     int8_t *s_dev = (int8_t *)(pt_dev + count * n);
     const DevCtx &d = c->dev;
     FHE_HIP(hipMemcpyAsync(s_dev, s, n, hipMemcpyHostToDevice, st));

@@ -57,3 +57,48 @@ def test_pieces(bits, t, count, big):
     bad[-1, -1] = t
     with pytest.raises(fhe.FheError):
         ctx.encrypt(fhe.from_numpy_u64(pk, "cuda"), bad, u, e)
+
+
+@pytest.mark.parametrize("t,count", [(65537, 1), (65537, 37), ((1 << 32) + 15, 37)])
+def test_workspace_is_used_and_held_to(t, count):
+    """The workspaces hold the rows that the calls keep (key and u, or s and c0 + c1 s)
+    and the client's words, nothing else, and nothing beyond them is written."""
+    import ctypes
+    import torch
+    qs = bfv.ntt_primes(N, 40, 2)
+    k = len(qs)
+    P = bfv.Params(N, qs, t, "coeff")
+    km = inputs.key_material(N, qs, 5)
+    pk, _ = bfv.keygen(P, km["s"], km["pk_a"], km["pk_e"], km["rlk_a"], km["rlk_e"])
+    ctx = fhe.Context(N, qs, t, "coeff")
+    L = fhe.lib()
+    rows = 8 * N
+    enc, dec = (L.fhe_workspace_bytes(ctx._h, op, count) for op in (fhe.OP_ENCRYPT, fhe.OP_DECRYPT))
+    assert enc <= rows * (2 * k + count * k + count) + 9 * N * count + 256
+    assert dec <= rows * (k + count * k + count) + N + 256
+    rng = np.random.default_rng(count)
+    pts = rng.integers(0, t, (count, N), dtype=np.uint64)
+    u = rng.integers(-1, 2, (count, N), dtype=np.int8)
+    e = rng.integers(-19, 20, (count, 2, N), dtype=np.int32)
+    pk_d = fhe.from_numpy_u64(pk, "cuda")
+    ct = torch.empty((count, 2, k, N), dtype=torch.int64, device="cuda")
+    back = np.empty_like(pts)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    guard = 4096
+    ws = torch.full((enc + guard,), 77, dtype=torch.uint8, device="cuda")
+    cast = lambda a, f, i: ctypes.cast(ptr(a), f.argtypes[i])  # noqa: E731
+    f = L.fhe_encrypt
+    assert f(ctx._h, pk_d.data_ptr(), cast(pts, f, 2), cast(u, f, 3), cast(e, f, 4), ct.data_ptr(), count,
+             ws.data_ptr(), enc, stream) == 0
+    assert (ws[enc:] == 77).all()
+    ws = torch.full((dec + guard,), 77, dtype=torch.uint8, device="cuda")
+    f = L.fhe_decrypt
+    s = np.ascontiguousarray(km["s"], dtype=np.int8)
+    assert f(ctx._h, cast(s, f, 1), ct.data_ptr(), cast(back, f, 3), count, ws.data_ptr(), dec, stream) == 0
+    assert (ws[dec:] == 77).all()
+    assert np.array_equal(back, pts)
+    got = ct.cpu().numpy().view(np.uint64)
+    for j in {0, count - 1}:
+        assert np.array_equal(got[j], bfv.encrypt(P, pk, pts[j], u[j], e[j])), j
+    assert f(ctx._h, cast(s, f, 1), ct.data_ptr(), cast(back, f, 3), count, ws.data_ptr(), dec - 1, stream) == -8
