@@ -73,3 +73,45 @@ def test_key_sums_of_eleven_digits(count):
     assert ctx.kernel_stats()["split_relin"][1] == 1
     for j in range(count):
         assert (got[j] == want[j % 3]).all(), j
+
+
+# (n, bits of the primes of Q, t, items of the large batch)
+SETS = [
+    (4096, (47, 47, 47, 47, 45), 2, 80),    # doubles, the largest primes without extra reductions
+    (4096, (49, 30), 17, 200),              # doubles, with them in Q and P
+    (8192, (43,) * 5, 65537, 40),           # doubles, 50-bit auxiliary primes
+    (16384, (50,), 17, 100),                # doubles, one prime next to 2^50
+    (16384, (47, 47, 47, 47, 43), 2, 20),   # doubles, fourteen levels without extra reductions
+    (16384, (55,) * 6, 65537, 17),          # integers: auxiliary primes too large for the lazy transforms
+    (16384, (55,) * 7, 65537, 14),          # that Q takes, the digits straight from the scale
+    (16384, (55,) * 8, 65537, 13),
+]
+
+
+@pytest.mark.parametrize("n,bits,t,many", SETS)
+def test_few_and_many_blocks(n, bits, t, many):
+    """Products and squares, in batches of three and of `many`, split and fused."""
+    qs = primes(n, bits)
+    k = len(qs)
+    print(f"[gpu-split-edges] n={n} bits={bits}", flush=True)
+    P, rlk, ctx, rlk_d = setup(n, qs, t)
+    K, NB = k + ctx.aux_primes, n // 1024
+    assert 3 * K * NB <= 3072 < many * K * NB and 3 * k * NB <= 1536 < many * k * NB
+    a, b = edge_cts(n, qs)
+    want_m = [bfv.mul_relin(P, a[j], b[j], rlk) for j in range(3)]
+    want_s = [bfv.mul_relin(P, a[j], a[j], rlk) for j in range(3)]
+    reps = (many + 2) // 3
+    da, db = up(a), up(b)
+    ba, bb = (x.repeat(reps, 1, 1, 1)[:many].contiguous() for x in (da, db))
+    ctx.set_timing(True)
+    for threshold in (2 ** 64 - 1, 0):  # never and always the fused kernels
+        ctx.set_fused_threshold(False, threshold)
+        ctx.set_fused_threshold(True, threshold)
+        ctx.reset_kernel_stats()
+        for x, y, want in ((da, db, want_m), (da, da, want_s), (ba, bb, want_m), (ba, ba, want_s)):
+            got = fhe.to_numpy_u64(ctx.mul_relin(rlk_d, x, y))
+            for j in range(got.shape[0]):
+                assert (got[j] == want[j % 3]).all(), (threshold, x is y, got.shape[0], j)
+        stats = ctx.kernel_stats()
+        assert stats["split_tensor"][1] == (0 if threshold == 0 else 4), stats
+        assert stats["split_relin"][1] == 4, stats
