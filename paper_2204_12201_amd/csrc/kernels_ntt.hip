@@ -742,8 +742,10 @@ __global__ __launch_bounds__(Geo<L>::T) void k_relin_fused(DevCtx c, const uint6
     relin_body<L, LAZY, RAW>(c, C2, rlk, out, blockIdx.y, (int)blockIdx.x, threadIdx.x, lds, true);
 }
 
-#ifndef FHE_NTT_L
+#if defined(FHE_NTT_L) && FHE_NTT_L == 14
 // ---- key switching of several parts (ring sizes) in one persistent launch --
+// (in the unit of n = 16384: beside it k_relin_fused<14> keeps five values in
+// scratch, compiled without it six)
 // Every workgroup (1024 threads, one row of 16384 words of LDS plus padding)
 // takes tasks from a queue until it is empty.  A task is one (item, limb)
 // row of a part at n = 16384, or two (n = 8192) or four (n = 4096)
@@ -976,6 +978,30 @@ const NttOps kOps = {NttL<FHE_NTT_L>::rows,          NttL<FHE_NTT_L>::fwd_ext,  
 #define FHE_CAT2(a, b) a##b
 #define FHE_CAT(a, b) FHE_CAT2(a, b)
 const NttOps *FHE_CAT(ntt_ops_, FHE_NTT_L)() { return &kOps; }
+#if FHE_NTT_L == 14
+
+hipError_t launch_relin_persist(const RelinQueue &Q, int lazy, int raw, unsigned int *queue, size_t tasks,
+                                hipStream_t s) {
+    if (Q.nparts <= 0 || tasks == 0) return hipSuccess;
+    auto kern = lazy ? (raw ? k_relin_persist<true, true> : k_relin_persist<true, false>)
+                     : k_relin_persist<false, false>;
+    if (!lazy && raw) return hipErrorInvalidValue;
+    static int resident = 0;  // workgroups the chip holds at once (same for every variant)
+    if (resident == 0) {
+        int nb = 0, dev = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 1024, 0) != hipSuccess ||
+            hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || nb < 1 ||
+            cus < 1)
+            return hipErrorInvalidValue;
+        resident = nb * cus;
+    }
+    const unsigned grid = (unsigned)(tasks < (size_t)resident ? tasks : (size_t)resident);
+    if (hipMemsetAsync(queue, 0, sizeof(unsigned int), s) != hipSuccess) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), 0, s, Q, queue);
+    return hipGetLastError();
+}
+#endif
 #else
 #define FHE_OPS(L) const NttOps *ntt_ops_##L();
 FHE_OPS(4) FHE_OPS(5) FHE_OPS(6) FHE_OPS(7) FHE_OPS(8) FHE_OPS(9) FHE_OPS(10) FHE_OPS(11) FHE_OPS(12) FHE_OPS(13)
@@ -1084,25 +1110,4 @@ hipError_t launch_relin_fused(const DevCtx &c, const uint64_t *C2, const uint64_
     return items ? o->relin_fused(c, C2, rlk, out, items, s) : hipSuccess;
 }
 
-hipError_t launch_relin_persist(const RelinQueue &Q, int lazy, int raw, unsigned int *queue, size_t tasks,
-                                hipStream_t s) {
-    if (Q.nparts <= 0 || tasks == 0) return hipSuccess;
-    auto kern = lazy ? (raw ? k_relin_persist<true, true> : k_relin_persist<true, false>)
-                     : k_relin_persist<false, false>;
-    if (!lazy && raw) return hipErrorInvalidValue;
-    static int resident = 0;  // workgroups the chip holds at once (same for every variant)
-    if (resident == 0) {
-        int nb = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, 1024, 0) != hipSuccess ||
-            hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || nb < 1 ||
-            cus < 1)
-            return hipErrorInvalidValue;
-        resident = nb * cus;
-    }
-    const unsigned grid = (unsigned)(tasks < (size_t)resident ? tasks : (size_t)resident);
-    if (hipMemsetAsync(queue, 0, sizeof(unsigned int), s) != hipSuccess) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), 0, s, Q, queue);
-    return hipGetLastError();
-}
 #endif
