@@ -488,11 +488,13 @@ bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     // without the matrix-core conversions the columns are not fused with them
     if (!c->dev.mx) return rows >= (size_t)256 << (14 - c->L);
     // products: the split kernels need four operand rows once where the fused
-    // one parks three (n = 16384, 16 items 470 against 481 us, 40: 1048 against
-    // 1182, 256: 5569 against 5772)
+    // one parks three (n = 16384, split against fused: 16 items, one whole round,
+    // 424 and 427 us, 32 781 and 773, 256 5776 and 5852; 24 597 and 692, 40 1055
+    // and 1109).  The autotuner's runs decide whole rounds either way
     if (!square) return false;
-    // squares: the fused kernel is up to 2 % faster in whole rounds (32 items: 585
-    // against 593 us) and loses the rest of a partial one (24: 540 against 506)
+    // squares: the fused kernel is 1 to 5 % faster in whole rounds (32 items: 609
+    // against 645 us, 256: 4590 against 4697) and loses the rest of a partial one
+    // (24: 541 against 492; 28, a fill of 0.875: equal)
     return fused_fill(c, rows) >= 0.93;
 }
 
@@ -518,9 +520,11 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
 }
 
 // Whether key switching of `items` ciphertexts takes the split kernels: always
-// in doubles; in integers they cost about 5 % more than whole rounds of the fused
-// kernel (n = 16384, 128 items: 2916 against 2797 us) and win where it leaves
-// the chip part empty (33 items, two rounds: 865 against 984; 56: equal).
+// in doubles; in integers a call costs 4 to 8 % more with them than with whole
+// rounds of the fused kernel, and less where that leaves the chip part empty
+// (squarings of n = 16384, split against fused key switching: 64 items 1333 and
+// 1249 us, 256 5171 and 4792; fills of 0.875 1188 and 1111 (56), 0.83 1678 and
+// 1663 (80), 0.75 998 and 1036 (48), 0.52 780 and 870 (33)).
 bool relin_is_split(const fhe_ctx *c, size_t items) {
     return c->relin_split_ok && (c->dev.f64 || fused_fill(c, items * c->k) < 0.85);
 }

@@ -349,7 +349,6 @@ __global__ __launch_bounds__(256) void k_split_tensor(DevCtx c, const uint64_t *
     constexpr int n = Geo<L>::N, NB = n / 1024, LAST = Geo<L>::NPASS - 1, NP = SQ ? 2 : 4;
     __shared__ V lds[SQ ? 3 : 4][kBlkWords];
     const int lane = threadIdx.x & 63, w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const size_t wpg = blockDim.x >> 6;  // waves: W or fewer
     const int limb = (int)blockIdx.x / NB, blk = (int)blockIdx.x % NB, K = c.K;
     const uint32_t tid = 64u * blk + lane;
     const size_t item = blockIdx.y;
