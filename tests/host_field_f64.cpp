@@ -230,7 +230,7 @@ struct Check {
                             for (auto &row : acc)
                                 for (double &a : row) a += v;
                         }
-                        if (few) f.acc_part(acc, k);
+                        if (few && k > 8) f.acc_part(acc);  // as the launch picks the kernel
                         sum += acc[1][7];
                         expect(std::fabs(sum) < LIMIT, "key sum bound", k, p, W);
                     }
