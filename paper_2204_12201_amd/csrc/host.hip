@@ -482,20 +482,33 @@ bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     if (thr != kFusedAuto) return rows >= thr;
     if (rows == c->tuned_rows[square ? 1 : 0]) return c->tuned_fused[square ? 1 : 0];
     // the fused kernels are integer ones: the floating-point field's split kernels
-    // are faster at every size (n = 8192, 341 items: 1790 against 2562 us fused in integers; n = 4096,
-    // 512: 829 against 1011)
+    // are faster at every size (n = 8192, 341 items: 1790 against 2562 us fused in
+    // integers; n = 4096, 512: 829 against 1011)
     if (c->dev.f64) return false;
     // without the matrix-core conversions the columns are not fused with them
     if (!c->dev.mx) return rows >= (size_t)256 << (14 - c->L);
-    // products: the split kernels need four operand rows once where the fused
-    // one parks three (n = 16384, split against fused: 16 items, one whole round,
-    // 424 and 427 us, 32 781 and 773, 256 5776 and 5852; 24 597 and 692, 40 1055
-    // and 1109).  The autotuner's runs decide whole rounds either way
+    // few rows: a wave per block spreads further than a workgroup per row (n =
+    // 16384, split against fused: 16 products of six primes 335 and 382 us)
+    if (rows * (c->n / 1024) <= kFewBlocks) return false;
+    // The columns of the split kernels cost the same for any basis of up to 8 (4)
+    // primes a side, so the fused kernels gain on them with every prime a basis has
+    // fewer than 16 (K), and lose what the last round leaves idle.  Split against
+    // fused, whole rounds of n = 16384, products: K = 16 5776 and 5852 us (256), 14
+    // 5451 and 5260, 12 4851 and 4467, 11 4167 and 3761, 9 3637 and 3049; squares: 4454
+    // and 4179 (K = 16), 4054 and 3387 (12), 2837 and 2275 (9); K = 12 at a fill of 0.66: 635
+    // and 693 (28 products).  Bases of at most four primes have their own columns:
+    // split is faster (K = 7: 2122 and 2247), but for squares with primes too
+    // large for the lazy transforms (K = 8, 128: 934 to 1000).
+    const double fill = fused_fill(c, rows), share = c->K / 16.0;
+    if (c->k <= 4 && c->kp <= 4) return square && c->L == 14 && !c->dev.lazy_all && fill >= 0.8;
+    if (c->L == 14) return fill >= share + (square ? -0.05 : 0.03);
+    // Rows of smaller rings share a CU, which hides more of their waits: products
+    // differ by 3 % either way (n = 8192, K = 12, 128: 1337 and 1312 us, K = 14, 256 7 %
+    // faster split), squares of n = 8192 gain up to twelve primes in full enough
+    // rounds (K = 11, 256: 1717 and 1561; K = 16: 5 % faster split), those of n = 4096
+    // always (K = 11, 128: 418 and 374; K = 14 546 and 509; K = 16: equal)
     if (!square) return false;
-    // squares: the fused kernel is 1 to 5 % faster in whole rounds (32 items: 609
-    // against 645 us, 256: 4590 against 4697) and loses the rest of a partial one
-    // (24: 541 against 492; 28, a fill of 0.875: equal)
-    return fused_fill(c, rows) >= 0.93;
+    return c->L == 12 || (c->K <= 12 && fill >= 0.65);
 }
 
 // Transform phase of `items` products (squares when a == b): P rows of E from

@@ -90,6 +90,13 @@ struct SplitOps {
 // The launches for ring degree 2^L, or null where there are none.
 const SplitOps *split_ops(int L);
 
+// Blocks of a launch up to which it is spread (one transform per wave) instead
+// of sharing the twiddles: four workgroups of the spread tensor kernel fill a
+// CU about three times over (products at n = 4096, 128 items: 268 against 272
+// us; n = 8192, 32: 240 against 248, 64: 463 against 436; n = 16384, 12: 405
+// against 419, 15: 516 against 493); key switching has half the blocks.
+constexpr size_t kFewBlocks = 3072;
+
 // ---- transforms (kernels_ntt.hip) ----
 // Launches of one ring degree (the launch_* functions below pick them by c.L).
 struct NttOps {

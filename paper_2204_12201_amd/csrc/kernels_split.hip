@@ -725,13 +725,6 @@ __global__ __launch_bounds__(kColThreads) void k_split_fin(DevCtx c, const uint6
     });
 }
 
-// Blocks of a launch up to which it is spread (one transform per wave) instead
-// of sharing the twiddles: four workgroups of the spread tensor kernel fill a
-// CU about three times over (products at n = 4096, 128 items: 268 against 272
-// us; n = 8192, 32: 240 against 248, 64: 463 against 436; n = 16384, 12: 405
-// against 419, 15: 516 against 493); key switching has half the blocks.
-constexpr size_t kFewBlocks = 3072;
-
 // A workgroup of W waves fills a CU (its LDS): item groups for about one
 // workgroup per CU, which then keeps its twiddles and its waves until the end.
 // Its waves: W, or as many as give every wave of every group the same number of
