@@ -533,13 +533,21 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
 }
 
 // Whether key switching of `items` ciphertexts takes the split kernels: always
-// in doubles; in integers a call costs 4 to 8 % more with them than with whole
-// rounds of the fused kernel, and less where that leaves the chip part empty
-// (squarings of n = 16384, split against fused key switching: 64 items 1333 and
-// 1249 us, 256 5171 and 4792; fills of 0.875 1188 and 1111 (56), 0.83 1678 and
-// 1663 (80), 0.75 998 and 1036 (48), 0.52 780 and 870 (33)).
+// in doubles; in integers where the fused kernel, a row per workgroup and CU at a
+// time, leaves CUs idle.  x: rows in rounds of 256; a number of primes that is a
+// power of two (p2) lets the split blocks of a prime stay on few XCDs.  Calls with
+// split against fused key switching (n = 16384, six and eight primes): x = 0.19
+// 0.65, 0.56 0.94, 0.75 1.04 (k = 6) and 0.93 (k = 8), 1.0 1.05, 1.12 0.94, 1.5 1.05
+// (k = 6) and 0.94 (k = 8), 2.25 1.01 and 0.96, above 1.0 to 1.1; n = 8192: 0.25 0.78,
+// 0.5 0.94 to 1, 0.75 1.08, 1.12 0.90, 1.5 1.0 and 0.92, above 1.0 to 1.09; n = 4096:
+// 0.25 0.82, 0.5 0.88, 0.75 0.99, above 1.0 to 1.06.
 bool relin_is_split(const fhe_ctx *c, size_t items) {
-    return c->relin_split_ok && (c->dev.f64 || fused_fill(c, items * c->k) < 0.85);
+    if (!c->relin_split_ok || c->dev.f64) return c->relin_split_ok;
+    const double x = (double)(items * c->k) / 256.0;
+    const bool p2 = (c->k & (c->k - 1)) == 0;
+    if (x <= 1.0) return x <= (c->L == 14 ? (p2 ? 0.75 : 0.68) : c->L == 13 ? (p2 ? 0.65 : 0.5) : 0.75);
+    const double rest = x - std::floor(x);
+    return c->L >= 13 && rest > 0 && (x <= 2.0 ? rest <= (p2 ? 0.5 : 0.32) : p2 && x <= 4.0 && rest <= 0.3);
 }
 
 // Key switching of C2 [items][k][n] added to out.  scratch: `words` words that

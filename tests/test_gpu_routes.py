@@ -36,24 +36,24 @@ def launches(ctx, call):
     return out, stats
 
 
-@pytest.mark.parametrize("n,k,items,square,fused", [
-    (16384, 4, 16, False, False),   # few rows
-    (16384, 4, 24, False, True),    # K = 9
-    (16384, 4, 32, False, False),   # a round and an eighth
-    (16384, 4, 56, False, True),
-    (16384, 6, 32, True, True),    # K = 12
-    (16384, 6, 48, False, False),
-    (16384, 8, 24, True, False),    # K = 16
-    (16384, 8, 32, True, True),
-    (16384, 8, 32, False, False),
-    (16384, 3, 32, True, False),    # at most four primes a side
-    (8192, 5, 64, True, True),      # K = 11
-    (8192, 5, 64, False, False),
-    (8192, 8, 64, True, False),
-    (4096, 5, 96, True, True),
-    (4096, 5, 32, True, False),
+@pytest.mark.parametrize("n,k,items,square,fused,relin_split", [
+    (16384, 4, 16, False, False, True),   # few rows
+    (16384, 4, 24, False, True, True),    # K = 9
+    (16384, 4, 32, False, False, True),   # a round and an eighth
+    (16384, 4, 56, False, True, False),
+    (16384, 6, 32, True, True, False),    # K = 12
+    (16384, 6, 48, False, False, True),
+    (16384, 8, 24, True, False, True),    # K = 16
+    (16384, 8, 32, True, True, False),
+    (16384, 8, 32, False, False, False),
+    (16384, 3, 32, True, False, True),    # at most four primes a side
+    (8192, 5, 64, True, True, True),      # K = 11
+    (8192, 5, 64, False, False, True),
+    (8192, 8, 64, True, False, False),
+    (4096, 5, 96, True, True, False),
+    (4096, 5, 32, True, False, True),
 ])
-def test_products(n, k, items, square, fused):
+def test_products(n, k, items, square, fused, relin_split):
     import torch
     print(f"[gpu-routes] n={n} k={k} items={items} square={square}", flush=True)
     ctx, rlk, a, b = setup(n, 55, k, 65537, items)
@@ -61,6 +61,7 @@ def test_products(n, k, items, square, fused):
     got, st = launches(ctx, lambda: ctx.mul_relin(rlk, a, y))
     assert (st["square_tensor" if square else "mul_tensor"] == 1) == fused, st
     assert (st["split_tensor"] == 1) == (not fused), st
+    assert (st["split_relin"] == 1, st["relin_fused"] == 1) == (relin_split, not relin_split), st
     ctx.set_fused_threshold(square, 2 ** 64 - 1 if fused else 0)
     other, st = launches(ctx, lambda: ctx.mul_relin(rlk, a, y))
     assert (st["split_tensor"] == 1) == fused, st
