@@ -631,6 +631,18 @@ fhe_status transform_operands(fhe_ctx *c, const uint64_t *a, uint64_t *That, siz
     return run(c, KK_FWD_EXT, s, [&] { return launch_fwd_ext(d, a, a, That, 2, items, s); });
 }
 
+// Whether the powers of the bridge (the largest batch of products: `items`) take
+// the split transforms.  Integer bases of more than four primes on a side and at
+// most 12 in all finish their transforms faster in whole rows once a batch fills the
+// chip (n = 16384, split against fused, 32 inputs, 256 products: K = 10 6723 and 5876 us,
+// 12 7339 and 7112; n = 8192, K = 9 3117 and 2914; four inputs 663 and 683), larger and
+// smaller ones and n = 4096 do not (K = 16 9256 and 9524; K = 7 3327 and 3623).
+bool powers_split(const fhe_ctx *c, size_t items) {
+    if (!c->split || !c->dev.mx) return false;
+    if (c->dev.f64 || c->L == 12 || (c->k <= 4 && c->kp <= 4) || c->K > 12) return true;
+    return items * c->n < ((size_t)64 << 14);
+}
+
 // Products of `count` items from transformed operands [.][2][K][n]
 // (transform_operands): item z multiplies input z mod na of Ahat by entry z of
 // Bhat; chunks of the batch cap, workspace as for products of two ciphertexts.
@@ -2351,7 +2363,7 @@ fhe_status fhe_bridge_to_bits_powers(fhe_ctx *c, const uint64_t *rlk, const uint
     std::vector<int32_t> W;
     bridge_weights(c->t, nbits, W);
     FHE_TRY(stage_weights(c, W.data(), nbits, c->t, wd, st));
-    const bool split = c->split && c->dev.mx;
+    const bool split = powers_split(c, hmax * gmax);
     for (size_t g0 = 0; g0 < count; g0 += G) {
         const size_t gc = count - g0 < G ? count - g0 : G;
         const size_t bw = gc * ctw;      // one power of every input of the group

@@ -66,3 +66,18 @@ def test_products(n, k, items, square, fused, relin_split):
     other, st = launches(ctx, lambda: ctx.mul_relin(rlk, a, y))
     assert (st["split_tensor"] == 1) == fused, st
     assert torch.equal(got, other)
+
+
+@pytest.mark.parametrize("n,bits,k,count,split", [
+    (8192, 43, 5, 4, True), (8192, 43, 5, 16, False), (8192, 43, 4, 16, True),
+    (16384, 55, 6, 8, False), (16384, 55, 6, 4, True), (16384, 55, 8, 8, True), (4096, 55, 5, 32, True),
+])
+def test_powers(n, bits, k, count, split):
+    import torch
+    print(f"[gpu-routes] powers n={n} k={k} count={count}", flush=True)
+    ctx, rlk, a, _ = setup(n, bits, k, 17, count)
+    got, st = launches(ctx, lambda: ctx.bridge_to_bits_powers(rlk, a, 5))
+    assert (st["split_tensor"] > 0) == split and (st["mul_tensor"] > 0) == (not split), st
+    one, st = launches(ctx, lambda: torch.cat([ctx.bridge_to_bits_powers(rlk, a[j:j + 1], 5) for j in range(2)]))
+    assert st["split_tensor"] > 0, st
+    assert torch.equal(got[:2], one)
