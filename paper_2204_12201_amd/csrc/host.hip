@@ -485,8 +485,11 @@ bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     // are faster at every size (n = 8192, 341 items: 1790 against 2562 us fused in
     // integers; n = 4096, 512: 829 against 1011)
     if (c->dev.f64) return false;
-    // without the matrix-core conversions the columns are not fused with them
-    if (!c->dev.mx) return rows >= (size_t)256 << (14 - c->L);
+    // without the matrix-core conversions the columns are not fused with them: split
+    // below a round (split against fused: n = 8192, ten primes, 24 products, 480 rows,
+    // 884 and 840 us; n = 4096, nine, 48 products, 864 rows, 759 and 728, 24 squares,
+    // 432 rows, 369 and 354)
+    if (!c->dev.mx) return rows >= (c->L == 14 ? 256u : c->L == 13 ? 448u : square ? 400u : 700u);
     // few rows: a wave per block spreads further than a workgroup per row (n =
     // 16384, split against fused: 16 products of six primes 335 and 382 us)
     if (rows * (c->n / 1024) <= kFewBlocks) return false;

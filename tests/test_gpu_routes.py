@@ -52,6 +52,8 @@ def launches(ctx, call):
     (8192, 8, 64, True, False, False),
     (4096, 5, 96, True, True, False),
     (4096, 5, 32, True, False, True),
+    (8192, 10, 24, True, True, False),    # more than eight primes
+    (8192, 10, 8, False, False, True),
 ])
 def test_products(n, k, items, square, fused, relin_split):
     import torch
