@@ -497,11 +497,11 @@ bool fused_wanted(const fhe_ctx *c, bool square, size_t items) {
     // primes a side, so the fused kernels gain on them with every prime a basis has
     // fewer than 16 (K), and lose what the last round leaves idle.  Split against
     // fused, whole rounds of n = 16384, products: K = 16 5776 and 5852 us (256), 14
-    // 5451 and 5260, 12 4851 and 4467, 11 4167 and 3761, 9 3637 and 3049; squares: 4454
-    // and 4179 (K = 16), 4054 and 3387 (12), 2837 and 2275 (9); K = 12 at a fill of 0.66: 635
-    // and 693 (28 products).  Bases of at most four primes have their own columns:
+    // 5451 and 5260, 12 4851 and 4467, 11 4167 and 3761, 9 3637 and 3049; squares: 4826
+    // and 4752 (K = 16), 3802 and 3387 (12), 2837 and 2275 (9); K = 12 at a fill of
+    // 0.66: 626 and 665 (28 products).  Bases of at most four primes have their own columns:
     // split is faster (K = 7: 2122 and 2247), but for squares with primes too
-    // large for the lazy transforms (K = 8, 128: 934 to 1000).
+    // large for the lazy transforms (K = 8, 128: 1165 and 1088).
     const double fill = fused_fill(c, rows), share = c->K / 16.0;
     if (c->k <= 4 && c->kp <= 4) return square && c->L == 14 && !c->dev.lazy_all && fill >= 0.8;
     if (c->L == 14) return fill >= share + (square ? -0.05 : 0.03);
@@ -537,13 +537,14 @@ fhe_status tensor_phase(fhe_ctx *c, const uint64_t *a, const uint64_t *b, uint64
 
 // Whether key switching of `items` ciphertexts takes the split kernels: always
 // in doubles; in integers where the fused kernel, a row per workgroup and CU at a
-// time, leaves CUs idle.  x: rows in rounds of 256; a number of primes that is a
-// power of two (p2) lets the split blocks of a prime stay on few XCDs.  Calls with
-// split against fused key switching (n = 16384, six and eight primes): x = 0.19
-// 0.65, 0.56 0.94, 0.75 1.04 (k = 6) and 0.93 (k = 8), 1.0 1.05, 1.12 0.94, 1.5 1.05
-// (k = 6) and 0.94 (k = 8), 2.25 1.01 and 0.96, above 1.0 to 1.1; n = 8192: 0.25 0.78,
-// 0.5 0.94 to 1, 0.75 1.08, 1.12 0.90, 1.5 1.0 and 0.92, above 1.0 to 1.09; n = 4096:
-// 0.25 0.82, 0.5 0.88, 0.75 0.99, above 1.0 to 1.06.
+// time, leaves CUs idle.  x: rows in rounds of 256.  Two, four and eight primes
+// (p2) measure better split up to fuller rounds than the numbers between; why was
+// not looked into.  Time of a call with split key switching over one with fused:
+//  n = 16384  x = 0.19: 0.65, 0.56: 0.94, 0.75: 1.04 (k = 6) and 0.93 (8), 1: 1.05,
+//             1.12: 0.94, 1.5: 1.05 (6) and 0.94 (8), 2.25: 1.01 and 0.96, more: 1 to 1.1
+//  n = 8192   0.25: 0.78, 0.5: 0.94 to 1, 0.75: 1.08, 1.12: 0.90, 1.5: 1.0 (6) and
+//             0.92 (8), more: 1 to 1.09
+//  n = 4096   0.25: 0.82, 0.5: 0.88, 0.75: 0.99, more: 1 to 1.06
 bool relin_is_split(const fhe_ctx *c, size_t items) {
     if (!c->relin_split_ok || c->dev.f64) return c->relin_split_ok;
     const double x = (double)(items * c->k) / 256.0;
