@@ -612,10 +612,8 @@ __device__ __forceinline__ void zero2(V (&acc)[2][16]) {
 // the workgroup; wave w takes digits w, w + W, ...; the waves' sums meet in LDS
 // (integers, or doubles holding integers below 2^53: any order gives the same
 // sum) and waves 0 and 1 finish one component each.  Dynamic LDS: W blocks and
-// 2048 words of sums.  PART: reduce the waves' sums before they meet (doubles,
-// more than eight digits; as a branch on k it cost the others 1.5 % of 64 products
-// at n = 4096).
-template <int L, class F, bool PART>
+// 2048 words of sums.
+template <int L, class F>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_split_relin(
     DevCtx c, const uint64_t *__restrict__ D, const uint64_t *__restrict__ rlk, uint64_t *__restrict__ R) {
     typedef typename F::V V;
@@ -639,7 +637,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
         for (int i = w; i < k; i += W, cnt++)
             digit_block<L, Fd>(f, D + ((item * k + i) * k + j) * (size_t)n, rlk + (((size_t)i * 2 + 0) * k + j) * n,
                                rlk + (((size_t)i * 2 + 1) * k + j) * n, acc, cnt, lds, lane, tid, tw);
-        if constexpr (PART) f.acc_part(acc);
 #pragma unroll
         for (int s = 0; s < 16; s++) {
             lds_add(&sums[s * 64 + lane], acc[0][s]);
@@ -838,12 +835,14 @@ struct SplitL {
         return digit_field(c, [&](auto fam, auto) {
             typedef decltype(fam) F;
             constexpr int WM = 12;
-            if (items * k * NB <= kFewBlocks / 2) {
+            // More than eight products modulo a prime of 2^47 or more can pass a
+            // double's 53 bits: only one wave's sum, reduced on the way, takes them.
+            // (Reducing the waves' sums first cost 64 products at n = 4096 1.5 %
+            // as a branch, and one at n = 16384 1 % as a kernel of its own.)
+            const bool sums_fit = !c.f64 || k <= 8 || !(c.big_limbs & ((1ull << k) - 1));
+            if (sums_fit && items * k * NB <= kFewBlocks / 2) {
                 const unsigned W = k < 8 ? (k < 2 ? 2 : (unsigned)k) : 8;
-                auto kern = k_split_relin<L, F, false>;
-                if constexpr (std::is_same<F, FamF>::value)
-                    if (k > 8) kern = k_split_relin<L, F, true>;
-                hipLaunchKernelGGL(kern, dim3((unsigned)k * NB, (unsigned)items), dim3(64 * W),
+                hipLaunchKernelGGL((k_split_relin<L, F>), dim3((unsigned)k * NB, (unsigned)items), dim3(64 * W),
                                    (W * kBlkWords + 2048) * 8, s, c, D, rlk, R);
             } else {
                 const ManyShape g = many_shape<WM>(k * NB, items);

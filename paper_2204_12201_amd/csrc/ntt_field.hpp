@@ -276,7 +276,6 @@ struct FieldU {
     template <int NR>
     __device__ __forceinline__ void key_operands(V (&)[NR][16]) const {}
     __device__ __forceinline__ void acc_mid(V (&)[2][16], int) const {}
-    __device__ __forceinline__ void acc_part(V (&)[2][16]) const {}
     __device__ __forceinline__ V key(uint64_t w) const { return w; }
     __device__ __forceinline__ V acc(V a, V x, V key) const { return a + mont_mul_lazy_u(x, key, q, qi); }
     __device__ __forceinline__ V acc_out(V a) const { return csub(csub(csub(a, q << 4), q << 3), q << 2); }
@@ -390,13 +389,11 @@ struct FieldF {
     // p (1/2 + 3/16), 3/(2 LIM) for the quotient's three roundings (mulvar_f);
     // eight of them, or eight and a reduced sum, stay below 8p.  Otherwise the
     // forward values reach 9.1p and a product 0.93p: 16 of them stay below 64p.
-    // acc_mid: before product number cnt of one wave's sum.
+    // acc_mid: before product number cnt of one wave's sum.  (Sums of several waves
+    // are of at most eight products: SplitL::relin.)
     __device__ __forceinline__ void acc_mid(V (&a)[2][16], int cnt) const {
         if ((cnt & 7) == 7) reduce_all(a);
     }
-    // before the sums of up to eight waves meet, if of more than eight products in
-    // all, which could pass 8p: eight reduced sums stay near 4p
-    __device__ __forceinline__ void acc_part(V (&a)[2][16]) const { reduce_all(a); }
     __device__ __forceinline__ V key(uint64_t w) const { return u52_to_f(w); }
     __device__ __forceinline__ V acc(V a, V x, V key) const { return a + mulvar_f(x, key, p, pinv); }
     __device__ __forceinline__ V acc_out(V a) const { return red_f(a, p, pinv); }

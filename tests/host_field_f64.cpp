@@ -218,7 +218,7 @@ struct Check {
         const F f(c, 0);
         for (int k = 1; k <= 16; k++)
             for (int sign = -1; sign <= 1; sign += 2)
-                for (int few = 0; few < 2; few++) {
+                for (int few = 0; few < (BIG && k > 8 ? 1 : 2); few++) {  // as the launch picks the kernel
                     const int W = !few ? 1 : k < 8 ? (k < 2 ? 2 : k) : 8;
                     const double v = sign * (2.0 * std::floor(prod * (double)p / 2) - 1);  // odd
                     double sum = 0.0;
@@ -230,7 +230,6 @@ struct Check {
                             for (auto &row : acc)
                                 for (double &a : row) a += v;
                         }
-                        if (few && k > 8) f.acc_part(acc);  // as the launch picks the kernel
                         sum += acc[1][7];
                         expect(std::fabs(sum) < LIMIT, "key sum bound", k, p, W);
                     }

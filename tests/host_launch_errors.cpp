@@ -1,12 +1,14 @@
 // Every launch of the split transforms must report its error.  The launch functions
 // of the runtime are replaced here, ahead of the library's: nothing reaches a device,
-// and of the launches of a call the one that `fail_at` names fails.
+// and of the launches of a call the one that `fail_at` names fails.  Their shapes tell
+// which kernel sums the keys: one wave an item where several could overflow a double.
 #include "kernels.hpp"
 
 #include <cstdio>
 
 static hipError_t last = hipSuccess;
 static int launches = 0, fail_at = 0;
+static unsigned first_block = 0;  // threads of a workgroup of a call's first launch
 
 extern "C" {
 hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
@@ -18,7 +20,10 @@ hipError_t hipGetLastError() {
     last = hipSuccess;
     return e;
 }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3 block, size_t, hipStream_t) {
+    if (launches == 0) first_block = block.x;
+    return hipSuccess;
+}
 hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
 }
 
@@ -62,6 +67,26 @@ int main() {
                 report("relin", [&] { return o.relin(c, p, p, p, p, items, nullptr); });
             }
         }
+    for (int L = 12; L <= 14; L++)
+        for (int k = 1; k <= 16; k++)
+            for (int big = 0; big < 3; big++) {  // no prime of 2^47 or more, one in Q, one in P
+                DevCtx c = {};
+                c.n = 1 << L;
+                c.L = L;
+                c.k = k;
+                c.kp = k;
+                c.K = 2 * k;
+                c.f64 = 1;
+                c.big_limbs = big ? 1ull << (big == 1 ? k - 1 : k) : 0;
+                launches = 0;
+                fail_at = -1;
+                split_ops(L)->relin(c, nullptr, nullptr, nullptr, nullptr, 1, nullptr);
+                const unsigned waves = k > 8 ? (big == 1 ? 1 : 8) : k < 2 ? 2 : k;
+                if (first_block != 64 * waves) {
+                    printf("key sums of %d digits: %u threads, L=%d big=%d\n", k, first_block, L, big);
+                    bad++;
+                }
+            }
     if (bad) return 1;
     printf("ok\n");
     return 0;

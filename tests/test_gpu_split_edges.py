@@ -52,7 +52,7 @@ def edge_cts(n, qs):
 @pytest.mark.parametrize("count", [3, 36])
 def test_key_sums_of_eleven_digits(count):
     """Key switching in doubles modulo a prime next to 2^50 with more digits than
-    eight, whose products meet in one sum: a small prime per further digit, and the
+    eight, which one wave sums: a small prime per further digit, and the
     first squaring of the bridge, whose workspace holds the digits (t = 3: it is the
     only one)."""
     n, t = 4096, 3

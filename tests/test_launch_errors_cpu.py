@@ -1,4 +1,4 @@
-"""A launch that fails is reported: every launch of the split transforms returns an
+"""A launch that fails is reported: every launch of the split transforms returns the
 error of the runtime (host_launch_errors.cpp, linked with the library, in place of
 the runtime's launch functions)."""
 import os
